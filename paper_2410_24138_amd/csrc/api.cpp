@@ -302,10 +302,11 @@ static int upload_problem(nls_handle* h) {
     return NLS_OK;
 }
 
-// LDS bytes of the fused local Newton kernel for subdomain i with LU variant v:
-// patch values, residual/step (and refinement vectors in mixed mode),
-// reduction scratch, multipliers, and the band window of the factorisation
-// (FP64 in every mode: the factorisation at the converged state is FP64).
+// The size measure of subdomain i with LU variant v, in LDS bytes, that the
+// buckets and the largest admissible subdomain are decided by: patch values,
+// residual/step (and refinement vectors in mixed mode), reduction scratch,
+// multipliers, and the band window of the factorisation (FP64 in every mode:
+// the factorisation at the converged state is FP64).
 static int local_lds_key(const HostMaps& M, int i, bool mixed, int v) {
     const int n = M.off_n[i + 1] - M.off_n[i], ng = M.off_g[i + 1] - M.off_g[i];
     const int dbl = (n + ng) + n + (mixed ? 2 * n : 0) + 24 + std::max(M.kl[i], 1) + 1;
@@ -324,18 +325,29 @@ static int solve_stage_bytes(int kl, int ku) {
     return 2 * 64 * (slots * 64 * 8 + 8);
 }
 
-// LDS bytes of a launch: the working set above, with the window region
-// grown (up to the 160 KB of a compute unit, less 1 KB for the kernels'
-// static LDS) so that it also holds the band solves' staging buffers.  The
-// kernel is limited to one workgroup per compute unit by its registers, so
-// the extra LDS costs no occupancy.
+// Bytes of the regrouped factorisation's two windows, 0 where its panel does
+// not fit a wavefront.
+static int gauss_want(int kl, int ku) {
+    return kl + 16 <= 64 ? gauss_window_bytes(kl, ku, 8) : 0;
+}
+
+// LDS bytes of a launch.  The patch values share the window's region (they
+// are not needed while a linear system is solved), which is grown (up to the
+// 160 KB of a compute unit, less 1 KB for the kernels' static LDS) to what
+// the factorisation and the solves' staging buffers can use.  The kernel is
+// limited to one workgroup per compute unit by its registers, so the extra
+// LDS costs no occupancy.
 static const int kLdsGrowCap = 159 * 1024;
 static int local_lds_bytes(const HostMaps& M, int i, bool mixed, int v) {
-    const int key = local_lds_key(M, i, mixed, v);
     const int n = M.off_n[i + 1] - M.off_n[i], ng = M.off_g[i + 1] - M.off_g[i];
-    const int base = ((n + ng) + n + (mixed ? 2 * n : 0) + 24 + std::max(M.kl[i], 1) + 1) * 8;
-    const int want = base + solve_stage_bytes(M.kl[i], M.ku[i]);
-    return std::max(key, std::min(want, kLdsGrowCap));
+    const int base = (n + (mixed ? 2 * n : 0) + 24 + std::max(M.kl[i], 1) + 1) * 8;
+    int w = band_window_doubles_v(M.kl[i], M.ku[i], v);
+    if (w < 0) w = band_window_doubles_v(M.kl[i], M.ku[i], 3);
+    const int least = base + std::max(n + ng, w) * 8;
+    const int gauss = v <= 1 ? gauss_want(M.kl[i], M.ku[i]) : 0;
+    int want = base + solve_stage_bytes(M.kl[i], M.ku[i]);
+    if (base + gauss <= kLdsGrowCap) want = std::max(want, base + gauss);
+    return std::max(least, std::min(want, kLdsGrowCap));
 }
 
 extern "C" int nls_set_partition(nls_handle* h, int32_t n_sub, const int32_t* elem_part,
@@ -614,14 +626,22 @@ extern "C" int nls_build_coarse(nls_handle* h, int kind, const double* u_lin) {
     }
     if (maxikl > 127 || maxiband > 256)
         return fail(h, NLS_ELIMIT, "interior band too wide");
-    const int lds_gdsw = C.max_ilds_doubles * 8 + 64;
+    int lds_gdsw = C.max_ilds_doubles * 8 + 64;
+    for (int i = 0; i < h->maps.nsub; ++i) {
+        const int ni = C.off_ni[i + 1] - C.off_ni[i];
+        const int want = (ni + 24 + std::max(C.ikl[i], 1) + 1) * 8 + gauss_want(C.ikl[i], C.iku[i]);
+        if (want <= kLdsGrowCap) lds_gdsw = std::max(lds_gdsw, want);
+    }
     int maxb = 0;
     for (size_t b = 0; b + 1 < C.boff.size(); ++b) maxb = std::max(maxb, C.boff[b + 1] - C.boff[b]);
-    h->lds_coarse_lu = (maxb + std::max(C.a0kl, 1) + 1 + band_window_doubles(C.a0kl, C.a0ku)) * 8;
+    const int coarse_base = (maxb + std::max(C.a0kl, 1) + 1) * 8;
+    h->lds_coarse_lu = coarse_base + band_window_doubles(C.a0kl, C.a0ku) * 8;
     // room for the solve's staged factor columns beyond the LU's window
     h->lds_coarse_lu = std::max(h->lds_coarse_lu,
                                 std::min(h->lds_coarse_lu + solve_stage_bytes(C.a0kl, C.a0ku),
                                          kLdsGrowCap));
+    if (coarse_base + gauss_want(C.a0kl, C.a0ku) <= kLdsGrowCap)
+        h->lds_coarse_lu = std::max(h->lds_coarse_lu, coarse_base + gauss_want(C.a0kl, C.a0ku));
     h->lds_coarse_q = maxnc * 8;
     if (lds_gdsw > 160 * 1024 || h->lds_coarse_lu > 160 * 1024 || h->lds_coarse_q > 160 * 1024)
         return fail(h, NLS_ELIMIT, "coarse working set exceeds LDS");

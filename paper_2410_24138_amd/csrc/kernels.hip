@@ -25,6 +25,7 @@
 #include <climits>
 #include <cfloat>
 #include <cmath>
+#include <type_traits>
 
 #include "nls.h"
 #include "nls_device.h"
@@ -976,6 +977,399 @@ __device__ __forceinline__ int band_lu_blocked(int n, int kl, int ku, const int*
     return sh[NB];
 }
 
+// A value that is the same in every lane, put where the compiler knows it: in
+// scalar registers.  (A table entry that is read after the kernel has stored
+// to memory comes through the vector loads.)
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+template <typename P>
+__device__ __forceinline__ P* uniform(P* p) {
+    const unsigned long long a = (unsigned long long)p;
+    const unsigned lo = (unsigned)uniform((int)(unsigned)a), hi = (unsigned)uniform((int)(a >> 32));
+    return (P*)(((unsigned long long)hi << 32) | lo);
+}
+
+// Stores through a buffer resource over [base, base + bytes): an offset past
+// its end is dropped by the hardware's range check, so a store that only some
+// lanes make needs no branch (those lanes take offset kNoStore).
+constexpr unsigned kNoStore = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t store_range(void* base, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(uniform(base), 0, uniform((int)bytes), 0x00020000);
+}
+__device__ __forceinline__ void range_store(__amdgpu_buffer_rsrc_t r, unsigned off, double v) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 d = {(unsigned)__double2loint(v), (unsigned)__double2hiint(v)};
+    __builtin_amdgcn_raw_buffer_store_b64(d, r, (int)off, 0, 0);
+}
+__device__ __forceinline__ void range_store(__amdgpu_buffer_rsrc_t r, unsigned off, float v) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)off, 0, 0);
+}
+
+// ----------------------------------------------------------------------------
+// The blocked band LU with its row operations regrouped for the matrix cores
+// (same pivoting rule and results layout as band_lu; 16-column panels, kl <=
+// 48).  The window of H = 16 + kl rows by 16 + kl + ku columns (in tiles of
+// 16, the rest zeros) sits in two LDS buffers: a panel reads one and writes the
+// shifted window into the other, so nothing is moved or cleared in between.  Wavefront 0 runs the chain of the panels; the other
+// wavefronts work beside it on what the next panel does not need yet:
+//  A  wavefront 0 factors the panel with one window row per lane and carries
+//     along G = [L11^{-1}; -L21 L11^{-1}], the panel's row operations as one
+//     H x 16 matrix: a step adds -l times the pivot row to the rows below, in
+//     the panel's columns right of the step and in G's columns left of it.
+//     It runs without a pivot search and compares the multipliers with 1
+//     afterwards (the pivot stays where no candidate is larger); only if one
+//     is larger, the panel is taken again with the search and the
+//     interchanges tracked as positions.  Meanwhile the others finish the
+//     panel before: column tiles 1.. of its update (into the window that this
+//     panel's first tile update will read: hence the barrier after step MID),
+//     the factors' entries and the 16 entering rows of the next window (their
+//     CSR entries fetched one panel ahead, row pointers two).  Wavefront 1
+//     makes all stores to memory and wavefronts 2 and 3 all loads: waits are
+//     counted over both, and a load would wait for the stores before it.
+//     Rows past n are identity rows, so the last panel is a full one.
+//  B  column tile 0 of [U12; A22'] = [0; A22] + G A12, the next panel's
+//     columns, one row tile of 16 per wavefront on 16x16x4 matrix-core steps,
+//     rows gathered by the panel's permutation.
+// Bound by wavefront 0's chain: per step 15 entries of the pivot row are
+// broadcast (two v_readlane and one FMA each, 14 cycles) and a reciprocal is
+// formed (41 cycles), about 5,400 cycles a panel.  Row strides are odd, so
+// that lanes in consecutive rows fall into different banks.  J_ii and its LU
+// of 256 subdomains of about 1,215 rows, kl = ku = 36: 0.31 ms (0.985 ms with
+// one window in place, the panel's search in every step and the three phases
+// in series); 705 rows, kl = ku = 36, one workgroup, with the solve: 0.26 ms
+// (0.73 ms).
+// ----------------------------------------------------------------------------
+template <typename T>
+__device__ __forceinline__ int band_lu_gauss(int n_, int kl_, int ku_, const int* __restrict__ rptr_,
+                                             const int* __restrict__ cols_,
+                                             const double* __restrict__ vals_, T* W, int* sh,
+                                             T* __restrict__ Uf, T* __restrict__ Lf,
+                                             int* __restrict__ piv_, int cbase, double* rhs) {
+    const int n = uniform(n_), kl = uniform(kl_), ku = uniform(ku_);
+    const int* __restrict__ rptr = uniform(rptr_);
+    const int* __restrict__ cols = uniform(cols_);
+    const double* __restrict__ vals = uniform(vals_);
+    int* __restrict__ piv = uniform(piv_);
+    constexpr int NB = 16, LG = NLS_GAUSS_LG, MID = 11;
+    typedef typename Mfma<T>::acc_t acc_t;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int H = NB + kl, ld = gauss_ld(kl, ku);
+    const int kw = kl + ku, ldu = kw + 1, ldl = kl > 1 ? kl : 1;
+    T* Wa = W;            // the window of the current panel
+    T* Wb = W + H * ld;   // the next one
+    T* Gs = Wb + H * ld;  // G by columns
+    T* Ps = Gs + NB * LG;        // the factored panel by columns, rows by their
+                                 // positions after the column's step (two
+                                 // copies, taken in turn)
+    int* sig = (int*)(Ps + 2 * NB * 64);  // position p of the panel holds row sig[p]
+    for (int e = tid; e < 2 * H * ld; e += NLS_BLOCK) Wa[e] = T(0);
+    if (tid == 0) sh[0] = 0;
+    __syncthreads();
+    for (int r = tid >> 2, q = tid & 3; r < H; r += NLS_BLOCK / 4) {
+        if (r < n) {
+            for (int s = rptr[r] + q; s < rptr[r + 1]; s += 4) {
+                const int c = cols[s] - cbase;
+                if (c < n) Wa[r * ld + c] = T(vals[s]);
+            }
+        } else if (q == 0) {
+            Wa[r * ld + r] = T(1);
+        }
+    }
+    // entering rows: lane 8 sl + t of wavefront 2 + w holds slots t, t + 8 and
+    // t + 16 of entering row 8 w + sl; rows with more entries are finished by
+    // the whole wavefront
+    constexpr int LPR = 8, RPW = 8, PF = 3;
+    const int et = lane & (LPR - 1), eq = RPW * (wv - 2) + lane / LPR;
+    int rs1 = 0, re1 = 0, rs2 = 0, re2 = 0;  // row pointers, next panel and the one after
+    int ec[PF];
+    double ev[PF];
+    auto load_ptr = [&](int k0, int& rs, int& re) {
+        const int r = k0 + H + eq;
+        rs = r < n ? rptr[r] : 0;
+        re = r < n ? rptr[r + 1] : 0;
+    };
+    auto load_ent = [&](int rs, int re) {
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            const int s = rs + et + LPR * u;
+            ec[u] = -1;
+            ev[u] = 0.0;
+            if (s < re) {
+                ec[u] = cols[s] - cbase;
+                ev[u] = vals[s];
+            }
+        }
+    };
+    const int li = lane & 15, lk = lane >> 4;
+    const int nrt = (H + 15) >> 4, nct = (kw + 15) >> 4;  // row and column tiles
+    const __amdgpu_buffer_rsrc_t Lr = store_range(Lf, (unsigned)(n * ldl) * sizeof(T));
+    const __amdgpu_buffer_rsrc_t Ur = store_range(Uf, (unsigned)(n * ldu) * sizeof(T));
+    // CT column tiles from ct (at most cb - 1 is kept) of row tile rt of
+    // [0; A22] + G A12 for the panel at k0, from the window src to the next
+    // one dst.  The products are formed transposed (rows across the lanes):
+    // a lane then reads the position of one row only, and a store of U12 (TOP,
+    // row tile 0) takes four columns' 16 consecutive entries.
+    auto tiles = [&](auto top, auto cts, int k0, const T* src, T* dst, int rt, int ct, int cb) {
+        constexpr bool TOP = decltype(top)::value;
+        constexpr int CT = decltype(cts)::value;
+        T ga[4], bv[CT][4];
+        acc_t acc[CT];
+        int sb[4];
+        const int r = 16 * rt + li;
+        const T* w = src + NB + 16 * ct;
+        const T* c = w + __umul24(sig[r], ld) + Mfma<T>::row(lk, 0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            sb[s] = __umul24(sig[4 * s + lk], ld);
+            ga[s] = Gs[(4 * s + lk) * LG + r];
+        }
+#pragma unroll
+        for (int u = 0; u < CT; ++u)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                bv[u][s] = w[sb[s] + 16 * u + li];
+                acc[u][s] = TOP ? T(0) : c[16 * u + Mfma<T>::row(0, s)];
+            }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int u = 0; u < CT; ++u) acc[u] = Mfma<T>::step(bv[u][s], ga[s], acc[u]);
+        if (TOP) {
+#pragma unroll
+            for (int u = 0; u < CT; ++u)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    // entry (row li, trailing column t); columns past kw are
+                    // more than kw above their row
+                    const int t = 16 * (ct + u) + Mfma<T>::row(lk, s), o = NB + t - li;
+                    range_store(Ur, o <= kw ? ((k0 + NB + t) * ldu + o) * (unsigned)sizeof(T) : kNoStore,
+                                acc[u][s]);
+                }
+        } else if (r < H) {
+            // (columns past kw receive zeros)
+            T* const d = dst + (r - NB) * ld + 16 * ct + Mfma<T>::row(lk, 0);
+#pragma unroll
+            for (int u = 0; u < CT; ++u)
+                if (u == 0 || ct + u < cb) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) d[16 * u + Mfma<T>::row(0, s)] = acc[u][s];
+                }
+        }
+    };
+    typedef std::integral_constant<bool, true> Top;
+    typedef std::integral_constant<bool, false> Below;
+    typedef std::integral_constant<int, 1> One;
+    typedef std::integral_constant<int, 2> Two;
+    // column tiles 1.. of the panel at k0 in pairs: U12 by wavefront 1, the
+    // row tiles below in turn by wavefronts 2 and 3, the right-hand side by 3
+    const int npair = nct >> 1;
+    auto trailing_top = [&](int k0, const T* src) {
+        for (int i = 0; i < npair; ++i) tiles(Top(), Two(), k0, src, (T*)nullptr, 0, 1 + 2 * i, nct);
+    };
+    auto trailing = [&](int k0, const T* src, T* dst) {
+        for (int i = wv - 2; i < (nrt - 1) * npair; i += 2) {
+            const int pair = i / (nrt - 1), rt = 1 + i - pair * (nrt - 1);
+            tiles(Below(), Two(), k0, src, dst, rt, 1 + 2 * pair, nct);
+        }
+    };
+    auto rhs_update = [&](int k0) {
+        const int r = sig[lane];
+        const double x = k0 + r < n ? rhs[k0 + r] : 0.0;
+        double y = lane < NB ? 0.0 : x;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) y += (double)Gs[k * LG + lane] * rdlane(x, k);
+        if (lane < H && k0 + lane < n) rhs[k0 + lane] = y;
+    };
+    // wavefront 1 writes the panel at k0 out of Ps: column j holds U11 down to
+    // the diagonal and the multipliers below it (columns past n lie outside
+    // the stores' range)
+    auto panel_out = [&](int k0) {
+#pragma unroll 4
+        for (int j = 0; j < NB; ++j) {
+            const T v = Ps[(k0 & NB) * 64 + j * 64 + lane];
+            const unsigned ou = j - lane, ol = lane - j - 1;
+            range_store(Ur, ou <= (unsigned)kw ? ((k0 + j) * ldu + ou) * (unsigned)sizeof(T) : kNoStore, v);
+            range_store(Lr, ol < (unsigned)kl ? ((k0 + j) * ldl + ol) * (unsigned)sizeof(T) : kNoStore, v);
+        }
+    };
+    __syncthreads();
+    // the roles run loops of their own, with the same barriers
+    if (wv == 0) {
+        bool search = false;
+        for (int k0 = 0; k0 < n; k0 += NB) {
+            // the lane number anew in every panel: the comparisons with it
+            // are cheaper taken again than kept in spilled scalar registers
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            const bool have = ln < H;
+            T* const Pk = Ps + (k0 & NB) * 64;
+            T p[NB], g[NB];
+            auto load = [&]() {
+                const T* row = Wa + (have ? ln : 0) * ld;
+#pragma unroll
+                for (int c = 0; c < NB; ++c) p[c] = row[c];
+#pragma unroll
+                for (int c = 0; c < NB; ++c) p[c] = have ? p[c] : T(0);
+            };
+            load();
+            int pos = ln, dsel = ln;  // dsel: lane j holds the pivot position of step j
+            bool redo = search;
+            if (!search) {
+                // no branch and no store between the steps.  The largest
+                // multiplier decides afterwards (the search takes entries
+                // within 2^-14 for equal); a zero pivot is left to the search
+                // as well.
+                T lmax = T(0), pmin = fabs(rdlane(p[0], 0));
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const T pv = rdlane(p[j], j);
+                    T pr[NB];  // the pivot row: panel right of j, G left of it
+#pragma unroll
+                    for (int c = 0; c < NB; ++c)
+                        if (c != j) pr[c] = rdlane(c > j ? p[c] : g[c], j);
+                    const T inv = recip(pv);
+                    const T lj = p[j] * inv;
+                    const T l = ln > j ? lj : T(0);
+                    p[j] = ln > j ? lj : p[j];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int c = j + 1; c < NB; ++c) p[c] -= l * pr[c];
+#pragma unroll
+                    for (int c = 0; c < j; ++c) g[c] -= l * pr[c];
+                    g[j] = ln == j ? T(1) : -l;
+                    lmax = fmax(lmax, fabs(l));
+                    pmin = fmin(pmin, fabs(pv));
+                    if (j == MID) lds_barrier();
+                }
+                redo = __ballot(lmax > T(1.0 + 0x1p-14)) != 0 || pmin == T(0);
+            }
+            if (!redo) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j) Pk[j * 64 + ln] = p[j];
+            } else {
+                if (search)
+                    lds_barrier();
+                else
+                    load();
+                int sing = 0;
+                bool used = false;
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    // candidates: the rows not yet chosen (rows below j + kl
+                    // hold zeros); a NaN or infinite entry has the largest key
+                    const bool cand = have && !used;
+                    const double av = fabs((double)p[j]);
+                    const int lj = __ffsll((unsigned long long)__ballot(have && pos == j)) - 1;
+                    const double aj = fabs((double)rdlane(p[j], lj));
+                    int d = j, pl = lj;
+                    if (__ballot(cand && av > aj) != 0) {
+                        d = __builtin_amdgcn_readfirstlane(
+                            wave_argmax_hi(cand ? (av <= DBL_MAX ? av : DBL_MAX) : -1.0, pos));
+                        pl = __ffsll((unsigned long long)__ballot(cand && pos == d)) - 1;
+                    }
+                    dsel = ln == j ? d : dsel;
+                    pos = pos == j ? d : (ln == pl ? j : pos);
+                    const T pv = rdlane(p[j], pl);
+                    sing |= pv == T(0) ? 1 : 0;
+                    const T inv = pv != T(0) ? recip(pv) : T(0);
+                    const T l = (cand && ln != pl) ? p[j] * inv : T(0);
+                    used = used || ln == pl;
+                    Pk[j * 64 + pos] = (cand && ln != pl) ? l : p[j];
+#pragma unroll
+                    for (int c = j + 1; c < NB; ++c) p[c] -= l * rdlane(p[c], pl);
+#pragma unroll
+                    for (int c = 0; c < j; ++c) g[c] -= l * rdlane(g[c], pl);
+                    g[j] = ln == pl ? T(1) : -l;
+                }
+                search = __ballot(have && pos != ln) != 0;
+                if (ln == 0 && sing) sh[0] = 1;
+            }
+#pragma unroll
+            for (int c = 0; c < NB; ++c) Gs[c * LG + pos] = g[c];
+            sig[pos] = have ? ln : 0;
+            lds_barrier();
+            if (ln < NB && k0 + ln < n) piv[k0 + ln] = k0 + dsel;
+            tiles(Top(), One(), k0, Wa, Wb, 0, 0, 1);
+            lds_barrier();
+            T* const tw = Wa;
+            Wa = Wb;
+            Wb = tw;
+        }
+    } else if (wv == 1) {
+        // stores to the factors, no loads: nothing here waits for memory
+        for (int k0 = 0; k0 < n; k0 += NB) {
+            if (k0 > 0) trailing_top(k0 - NB, Wb);
+            lds_barrier();
+            if (k0 > 0) panel_out(k0 - NB);
+            for (int r = lk; r < kl; r += 4) Wb[r * ld + 16 * nct + li] = T(0);
+            lds_barrier();
+            if (nrt > 1) tiles(Below(), One(), k0, Wa, Wb, 1, 0, 1);
+            lds_barrier();
+            T* const tw = Wa;
+            Wa = Wb;
+            Wb = tw;
+        }
+        const int kl0 = (n - 1) / NB * NB;
+        if (n > 0) panel_out(kl0);
+        if (rhs && n > 0) rhs_update(kl0);
+    } else {
+        // loads of the entering rows, no stores to memory
+        load_ptr(0, rs1, re1);
+        load_ent(rs1, re1);
+        load_ptr(NB, rs2, re2);
+        for (int k0 = 0; k0 < n; k0 += NB) {
+            const int k1 = k0 + NB;
+            if (k0 > 0) {
+                if (rhs && wv == 3) rhs_update(k0 - NB);
+                trailing(k0 - NB, Wb, Wa);
+            }
+            lds_barrier();
+            T* const E = Wb + (kl + RPW * (wv - 2)) * ld;
+            for (int c = lane; c < RPW * ld; c += 64) E[c] = T(0);
+#pragma unroll
+            for (int u = 0; u < PF; ++u)
+                if (ec[u] >= 0 && ec[u] < n) Wb[(kl + eq) * ld + (ec[u] - k1)] = T(ev[u]);
+            if (et == 0 && k0 + H + eq >= n) Wb[(kl + eq) * ld + kl + eq] = T(1);
+            if (__ballot(re1 - rs1 > PF * LPR) != 0) {
+                for (int w = 0;; w += 64) {
+                    int xc[RPW];
+                    double xv[RPW];
+                    bool more = false;
+#pragma unroll
+                    for (int u = 0; u < RPW; ++u) {
+                        const int rs = __builtin_amdgcn_readlane(rs1, LPR * u),
+                                  re = __builtin_amdgcn_readlane(re1, LPR * u);
+                        const int s = rs + PF * LPR + w + lane;
+                        xc[u] = -1;
+                        xv[u] = 0.0;
+                        if (s < re) {
+                            xc[u] = cols[s] - cbase;
+                            xv[u] = vals[s];
+                        }
+                        more = more || rs + PF * LPR + w + 64 < re;
+                    }
+#pragma unroll
+                    for (int u = 0; u < RPW; ++u)
+                        if (xc[u] >= 0 && xc[u] < n) E[u * ld + (xc[u] - k1)] = T(xv[u]);
+                    if (!more) break;
+                }
+            }
+            rs1 = rs2;
+            re1 = re2;
+            load_ent(rs1, re1);
+            load_ptr(k1 + NB, rs2, re2);
+            lds_barrier();
+            if (wv < nrt) tiles(Below(), One(), k0, Wa, Wb, wv, 0, 1);
+            lds_barrier();
+            T* const tw = Wa;
+            Wa = Wb;
+            Wb = tw;
+        }
+    }
+    __syncthreads();  // factors in HBM are complete for the workgroup
+    return sh[0];
+}
+
 // Choose the blocked factorization when its panel fits a wavefront.
 // With rhs (length n, LDS), the row operations are applied to it as well,
 // so that it leaves holding the forward-substituted L^{-1} P rhs.
@@ -983,10 +1377,13 @@ template <typename T>
 __device__ __forceinline__ int band_lu_auto(int n, int kl, int ku, const int* __restrict__ rptr,
                             const int* __restrict__ cols, const double* __restrict__ vals,
                             T* W, T* mult, int* sflag, T* __restrict__ Uf, T* __restrict__ Lf,
-                            int* __restrict__ piv, int cbase = 0, int variant = 0,
+                            int* __restrict__ piv, int wbytes, int cbase = 0, int variant = 0,
                             double* rhs = nullptr, bool bf16 = false) {
     // variant: 0 widest panel the band allows, 1 NB=16, 2 NB=8, 3 unblocked
-    // (bf16 trailing updates exist in the blocked forms only)
+    // (bf16 trailing updates exist in the blocked forms only).  The 16-column
+    // panels take the regrouped form wherever its two windows fit the wbytes
+    // at W; a subdomain so large that they do not (some 2,000 rows at kl =
+    // 48, 5,000 at kl = 36) keeps the single window.
     if constexpr (sizeof(T) == 4) {
         if (bf16) {
             if ((variant == 0 || variant == 1) && kl + 16 <= 64)
@@ -997,6 +1394,9 @@ __device__ __forceinline__ int band_lu_auto(int n, int kl, int ku, const int* __
                                                    piv, cbase, rhs);
         }
     }
+    if ((variant == 0 || variant == 1) && kl + 16 <= 64 &&
+        gauss_window_bytes(kl, ku, (int)sizeof(T)) <= wbytes)
+        return band_lu_gauss<T>(n, kl, ku, rptr, cols, vals, W, sflag, Uf, Lf, piv, cbase, rhs);
     if ((variant == 0 || variant == 1) && kl + 16 <= 64)
         return band_lu_blocked<T, 16>(n, kl, ku, rptr, cols, vals, W, sflag, Uf, Lf, piv, cbase, rhs);
     if ((variant == 0 || variant == 2) && kl + 8 <= 64)
@@ -1011,14 +1411,13 @@ __device__ __forceinline__ int band_lu_auto(int n, int kl, int ku, const int* __
 // steps, and the next chunk's loads are issued before the current chunk's
 // steps run, so their HBM latency overlaps those steps.
 // ----------------------------------------------------------------------------
-template <typename T, int NPL>
+template <typename T, int NPL, bool FORWARD_ONLY = false>
 __device__ __forceinline__ void band_solve_wave(int n, int kl, int ku, const T* __restrict__ Uf,
-                                const T* __restrict__ Lf, const int* __restrict__ piv,
-                                double* b, bool backward_only = false) {
+                                const T* __restrict__ Lf, const int* __restrict__ piv, double* b) {
     constexpr int S = 8;
     const int lane = threadIdx.x & 63;
     const int ldu = kl + ku + 1, ldl = kl > 1 ? kl : 1;
-    if (!backward_only && n > 0) {
+    if (n > 0) {
         T ln[S][NPL];  // columns of L and pivots of the next chunk, as loaded
         int pn[S];
         auto fetch_l = [&](int k0) {
@@ -1069,7 +1468,7 @@ __device__ __forceinline__ void band_solve_wave(int n, int kl, int ku, const T* 
             }
         }
     }
-    if (n > 0) {
+    if (!FORWARD_ONLY && n > 0) {
         T un[S][NPL];  // columns of U (above the diagonal) of the next chunk
         T dn[S];       // and their diagonal entries, as loaded
         auto fetch_u = [&](int k0) {
@@ -1118,26 +1517,24 @@ __device__ __forceinline__ void band_solve_wave(int n, int kl, int ku, const T* 
 }
 
 // ----------------------------------------------------------------------------
-// Band triangular solves with the factors of band_lu for one right-hand side
-// b (LDS, FP64), carried out by the whole workgroup.  Wavefront 0 runs the
+// Forward substitution with the factors of band_lu for one right-hand side b
+// (LDS, FP64), carried out by the whole workgroup.  Wavefront 0 runs the
 // substitution steps with the rows of b that a step can touch in registers:
-// R = NPL + 1 slots of 64 rows (the kl + ku <= 64 NPL rows next to step k lie
-// in blocks k / 64 -+ 0..R-1), slot 0 holding the block of row k.  A step
+// R = NPL + 1 slots of 64 rows (the kl <= 64 NPL rows below step k lie in
+// blocks k / 64 .. k / 64 + R - 1), slot 0 holding the block of row k.  A step
 // broadcasts the finished entry with v_readlane, keeps it in slot 0 and
 // updates every slot with one FMA; when the step leaves a block, the block
 // goes to b and the slots move by one, the last one taking the next block
-// from b.  The other wavefronts stage the next G steps' factor entries into
-// one half of an LDS double buffer while wavefront 0 reads the other half,
-// already in slot order (entry (q, l) of a column is the factor entry of the
-// row that lane l of slot q holds, zero outside the band) with the pivots or
-// the reciprocals of the diagonal beside them, so that a step reads one entry
-// per slot and applies no masks.  The workgroup synchronises every G steps.
-// Same arithmetic, in the same order, as the one-wavefront solve above.  All
-// threads of the workgroup call it.
+// from b.  The other wavefronts stage the next G steps' multipliers into one
+// half of an LDS double buffer while wavefront 0 reads the other half, already
+// in slot order (entry (q, l) of a column is the multiplier of the row that
+// lane l of slot q holds, zero outside the band) with the pivots beside them,
+// so that a step reads one entry per slot and applies no masks.  The workgroup
+// synchronises every G steps.  All threads of the workgroup call it.
 // ----------------------------------------------------------------------------
 template <typename T, int NPL>
 __host__ __device__ __forceinline__ int band_stage_col_bytes() {
-    return (NPL + 1) * 64 * (int)sizeof(T) + 8;  // slot entries + pivot or 1/d
+    return (NPL + 1) * 64 * (int)sizeof(T) + 8;  // slot entries + pivot
 }
 template <typename T, int NPL>
 __device__ __forceinline__ int band_stage_cols(int stage_bytes) {
@@ -1198,15 +1595,14 @@ struct BandRing {
 };
 
 template <typename T, int NPL>
-__device__ __forceinline__ void band_solve_staged(int n, int kl, int ku, const T* __restrict__ Uf,
-                                                  const T* __restrict__ Lf,
-                                                  const int* __restrict__ piv, double* b,
-                                                  void* stage, int G, bool backward_only) {
+__device__ __forceinline__ void band_forward_staged(int n, int kl, int ku, const T* __restrict__ Lf,
+                                                    const int* __restrict__ piv, double* b,
+                                                    void* stage, int G) {
     constexpr int R = NPL + 1, S = 4, CB = 8, PER = R * 64;
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63;
-    const int ldu = kl + ku + 1, ldl = kl > 1 ? kl : 1, bw = kl + ku;
+    const int ldl = kl > 1 ? kl : 1;
     const int t0 = nt > 64 ? 64 : 0;  // first thread of the staging waves
-    // buffer h: G columns of PER entries, then G pivots or reciprocals
+    // buffer h: G columns of PER entries, then G pivots
     T* sE[2] = {(T*)stage, (T*)stage + G * PER};
     double* sD[2] = {(double*)((T*)stage + 2 * G * PER), (double*)((T*)stage + 2 * G * PER) + G};
     BandRing<R> ring;
@@ -1243,189 +1639,244 @@ __device__ __forceinline__ void band_solve_staged(int n, int kl, int ku, const T
         }
     };
     if (n <= 0) return;
-    if (!backward_only) {
-        // forward: slot q holds block k / 64 + q; entry (q, l) of column k is
-        // the multiplier of row 64 (k / 64 + q) + l at step k
-        auto stage_l = [&](int h, int c0, int first) {
-            const int cnt = min(c0 + G, n) - c0;
-            stage_entries(sE[h], c0, cnt, first, [&](int k, int q, int l, bool& ok) {
-                const int j = 64 * ((k >> 6) + q) + l - k - 1;
-                ok = j >= 0 && j < min(kl, n - 1 - k);
-                return Lf[(size_t)k * ldl + (ok ? j : 0)];
-            });
-            if (tid >= first)
-                for (int c = tid - first; c < cnt; c += nt - first)
-                    ((int*)sD[h])[c] = piv[c0 + c];
-        };
-        stage_l(0, 0, 0);
-        __syncthreads();
-        if (tid < 64) {
-#pragma unroll
-            for (int q = 0; q < R; ++q) ring.set(q, block(q));
-        }
-        for (int c0 = 0, h = 0; c0 < n; c0 += G, h ^= 1) {
-            const int c1 = min(c0 + G, n);
-            if (c1 < n) stage_l(h ^ 1, c1, t0);
-            if (tid < 64) {
-                const T* E = sE[h];
-                const int* pvs = (const int*)sD[h];
-                T ln[S][R];
-                int pn[S];
-                auto fetch = [&](int k) {
-#pragma unroll
-                    for (int t = 0; t < S; ++t) {
-                        const int ck = min(k + t, c1 - 1) - c0;
-                        pn[t] = pvs[ck];
-#pragma unroll
-                        for (int q = 0; q < R; ++q) ln[t][q] = E[ck * PER + q * 64 + lane];
-                    }
-                };
-                fetch(c0);
-                for (int k0 = c0; k0 < c1; k0 += S) {
-                    double lv[S][R];
-                    int pv[S];
-#pragma unroll
-                    for (int t = 0; t < S; ++t) {
-                        pv[t] = pn[t];
-#pragma unroll
-                        for (int q = 0; q < R; ++q) lv[t][q] = (double)ln[t][q];
-                    }
-                    if (k0 + S < c1) fetch(k0 + S);
-#pragma unroll
-                    for (int t = 0; t < S; ++t) {
-                        const int k = k0 + t;
-                        if (k < c1) {
-                            const int lk = k & 63;
-                            // entering block k / 64: the finished block leaves
-                            if (lk == 0 && k > 0) {
-                                flush((k >> 6) - 1);
-                                ring.shift(block((k >> 6) + R - 1));
-                            }
-                            const int p = __builtin_amdgcn_readfirstlane(pv[t]);
-                            const double bk = rdlane(ring.s0, lk);
-                            double x = bk;
-                            if (p != k) {
-                                // interchange rows k and p: row p takes b_k
-                                const int qp = (p >> 6) - (k >> 6), lp = p & 63;
-                                x = ring.lane_value(qp, lp);
-                                ring.put(qp, lane == lp, bk);
-                            }
-                            ring.axpy(lv[t], x);  // zero at row k itself
-                            ring.s0 = lane == lk ? x : ring.s0;
-                        }
-                    }
-                }
-                if (c1 == n) flush((n - 1) >> 6);
-            }
-            __syncthreads();
-        }
-    }
-    // backward: U x = b from the last column down; slot q holds block
-    // k / 64 - q; entry (q, l) of column k is U(row, k) for the row
-    // 64 (k / 64 - q) + l above the diagonal, and the reciprocal of U(k, k)
-    // sits beside the column
-    auto stage_u = [&](int h, int c1, int first) {
-        const int c0 = max(c1 - G, 0), cnt = c1 - c0;
+    // forward: slot q holds block k / 64 + q; entry (q, l) of column k is
+    // the multiplier of row 64 (k / 64 + q) + l at step k
+    auto stage_l = [&](int h, int c0, int first) {
+        const int cnt = min(c0 + G, n) - c0;
         stage_entries(sE[h], c0, cnt, first, [&](int k, int q, int l, bool& ok) {
-            const int off = k - 64 * ((k >> 6) - q) - l;
-            ok = off >= 1 && off <= min(bw, k);
-            return Uf[(size_t)k * ldu + (ok ? off : 0)];
+            const int j = 64 * ((k >> 6) + q) + l - k - 1;
+            ok = j >= 0 && j < min(kl, n - 1 - k);
+            return Lf[(size_t)k * ldl + (ok ? j : 0)];
         });
         if (tid >= first)
             for (int c = tid - first; c < cnt; c += nt - first)
-                sD[h][c] = 1.0 / (double)Uf[(size_t)(c0 + c) * ldu];
+                ((int*)sD[h])[c] = piv[c0 + c];
     };
-    stage_u(0, n, 0);
+    stage_l(0, 0, 0);
     __syncthreads();
     if (tid < 64) {
-        const int Btop = (n - 1) >> 6;
 #pragma unroll
-        for (int q = 0; q < R; ++q) ring.set(q, block(Btop - q));
+        for (int q = 0; q < R; ++q) ring.set(q, block(q));
     }
-    for (int c1 = n, h = 0; c1 > 0; c1 -= G, h ^= 1) {
-        const int c0 = max(c1 - G, 0);
-        if (c0 > 0) stage_u(h ^ 1, c0, t0);
+    for (int c0 = 0, h = 0; c0 < n; c0 += G, h ^= 1) {
+        const int c1 = min(c0 + G, n);
+        if (c1 < n) stage_l(h ^ 1, c1, t0);
         if (tid < 64) {
             const T* E = sE[h];
-            const double* D = sD[h];
-            T un[S][R];
-            double dn[S];
+            const int* pvs = (const int*)sD[h];
+            T ln[S][R];
+            int pn[S];
             auto fetch = [&](int k) {
 #pragma unroll
                 for (int t = 0; t < S; ++t) {
-                    const int ck = max(k - t, c0) - c0;
-                    dn[t] = D[ck];
+                    const int ck = min(k + t, c1 - 1) - c0;
+                    pn[t] = pvs[ck];
 #pragma unroll
-                    for (int q = 0; q < R; ++q) un[t][q] = E[ck * PER + q * 64 + lane];
+                    for (int q = 0; q < R; ++q) ln[t][q] = E[ck * PER + q * 64 + lane];
                 }
             };
-            fetch(c1 - 1);
-            for (int k0 = c1 - 1; k0 >= c0; k0 -= S) {
-                double uv[S][R], rdg[S];
+            fetch(c0);
+            for (int k0 = c0; k0 < c1; k0 += S) {
+                double lv[S][R];
+                int pv[S];
 #pragma unroll
                 for (int t = 0; t < S; ++t) {
-                    rdg[t] = dn[t];
+                    pv[t] = pn[t];
 #pragma unroll
-                    for (int q = 0; q < R; ++q) uv[t][q] = (double)un[t][q];
+                    for (int q = 0; q < R; ++q) lv[t][q] = (double)ln[t][q];
                 }
-                if (k0 - S >= c0) fetch(k0 - S);
+                if (k0 + S < c1) fetch(k0 + S);
 #pragma unroll
                 for (int t = 0; t < S; ++t) {
-                    const int k = k0 - t;
-                    if (k >= c0) {
+                    const int k = k0 + t;
+                    if (k < c1) {
                         const int lk = k & 63;
-                        const double xk = rdlane(ring.s0, lk) * rdg[t];
-                        ring.axpy(uv[t], xk);  // zero at row k itself
-                        ring.s0 = lane == lk ? xk : ring.s0;
-                        // block k / 64 is finished: to b, and the slots move
-                        if (lk == 0) {
-                            flush(k >> 6);
-                            if (k > 0) ring.shift(block((k >> 6) - R));
+                        // entering block k / 64: the finished block leaves
+                        if (lk == 0 && k > 0) {
+                            flush((k >> 6) - 1);
+                            ring.shift(block((k >> 6) + R - 1));
                         }
+                        const int p = __builtin_amdgcn_readfirstlane(pv[t]);
+                        const double bk = rdlane(ring.s0, lk);
+                        double x = bk;
+                        if (p != k) {
+                            // interchange rows k and p: row p takes b_k
+                            const int qp = (p >> 6) - (k >> 6), lp = p & 63;
+                            x = ring.lane_value(qp, lp);
+                            ring.put(qp, lane == lp, bk);
+                        }
+                        ring.axpy(lv[t], x);  // zero at row k itself
+                        ring.s0 = lane == lk ? x : ring.s0;
                     }
                 }
             }
+            if (c1 == n) flush((n - 1) >> 6);
         }
         __syncthreads();
     }
 }
 
-// The workgroup's band solve: staged when the stage holds 8 or more steps,
-// otherwise the one-wavefront solve.  All threads call it; b is complete for
-// every thread on return.
+// Loads through a buffer resource: an offset past its end gives 0.
+__device__ __forceinline__ double range_load(__amdgpu_buffer_rsrc_t r, unsigned off, double) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 d = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+    return __hiloint2double((int)d[1], (int)d[0]);
+}
+__device__ __forceinline__ float range_load(__amdgpu_buffer_rsrc_t r, unsigned off, float) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+
+// Sum over the four lanes l, l ^ 16, l ^ 32, l ^ 48, in all of them.
+__device__ __forceinline__ double sum_rows16(double v) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+    u32x2 hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+    v = __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+    lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+    hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+// ----------------------------------------------------------------------------
+// Backward substitution U x = b (b in LDS, FP64, in place) with the factors
+// of band_lu, by the whole workgroup in blocks of 16 rows from the last one
+// up: x_1 = U11^{-1} (b_1 - U12 x_2).  Wavefront t mod 4 takes block t (t = 0
+// the last): lane (r, p) = (l mod 16, l / 16) holds the entries of row r in
+// the columns 4 i + p of the block's strip, NC of them, and the whole row r of
+// U11, scaled by the reciprocal diagonal.  A block's entries are loaded AHEAD
+// rounds of four blocks ahead (two where the registers hold them); the products with all but the next block's
+// unknowns are summed one block ahead; so between two blocks lie four of the
+// products, a sum over four lanes, and U11's 16 steps of a broadcast and an
+// FMA each (1,215 rows, kl = ku = 36: 0.03 ms; 0.2 ms step by step from
+// staged columns, which waited for memory).  All threads call it; b is
+// complete for every thread on return.
+// ----------------------------------------------------------------------------
+template <typename T, int NC, int AHEAD>
+__device__ __forceinline__ void band_back_blocked(int n_, int kw_, const T* Uf, double* b) {
+    const int n = uniform(n_), kw = uniform(kw_), ldu = kw + 1;
+    const int lane = threadIdx.x & 63, wv = uniform((int)(threadIdx.x >> 6));
+    const int r = lane & 15, p = lane >> 4, nb = (n + 15) >> 4;
+    const __amdgpu_buffer_rsrc_t Ur = store_range(const_cast<T*>(Uf), (unsigned)(n * ldu) * sizeof(T));
+    struct Block {
+        T u[NC - 4];  // columns 16 + 4 i + p of the strip
+        T u11[16];    // the row of U11
+        T d;          // its diagonal entry
+    };
+    Block A, B;
+    double far_sum = 0.0;
+    auto load = [&](Block& S, int t) {
+        const int k0 = 16 * (nb - 1 - t);
+        if (k0 < 0) return;
+#pragma unroll
+        for (int i = 4; i < NC; ++i) {
+            const unsigned c = 4 * i + p, o = c - r;
+            S.u[i - 4] = range_load(
+                Ur, o <= (unsigned)kw ? ((k0 + c) * ldu + o) * (unsigned)sizeof(T) : kNoStore, T());
+        }
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+            const unsigned o = c - r;
+            S.u11[c] = range_load(
+                Ur, o <= (unsigned)kw ? ((k0 + c) * ldu + o) * (unsigned)sizeof(T) : kNoStore, T());
+        }
+        S.d = range_load(Ur, (k0 + r) * ldu * (unsigned)sizeof(T), T());
+    };
+    auto products = [&](const Block& S, int k0, int i0, int i1) {
+        double acc = 0.0;
+#pragma unroll
+        for (int i = 4; i < NC; ++i)
+            if (i >= i0 && i < i1) acc += (double)S.u[i - 4] * b[min(k0 + 4 * i + p, n - 1)];
+        return acc;
+    };
+    auto far_part = [&](const Block& S, int t) {
+        if (t < nb) far_sum = products(S, 16 * (nb - 1 - t), 8, NC);
+    };
+    auto near_part = [&](Block& S, int t) {
+        if (t >= nb) return;
+        const int k0 = 16 * (nb - 1 - t);
+        const bool in = k0 + r < n;
+        const double rd = in ? 1.0 / (double)S.d : 0.0;
+        double w[16];
+#pragma unroll
+        for (int c = 1; c < 16; ++c) w[c] = c > r ? (double)S.u11[c] * rd : 0.0;
+        double z = b[in ? k0 + r : k0];
+        z = (z - sum_rows16(far_sum + products(S, k0, 4, 8))) * rd;
+#pragma unroll
+        for (int c = 15; c > 0; --c) z -= w[c] * rdlane(z, c);
+        if (lane < 16 && in) b[k0 + r] = z;
+        load(S, t + 4 * AHEAD);
+    };
+    load(A, wv);
+    if (AHEAD == 2) load(B, wv + 4);
+    auto round = [&](Block& S, Block& next, int t0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (wv == q)
+                near_part(S, t0 + q);
+            else if (wv == q + 1)
+                far_part(S, t0 + q + 1);
+            else if (q == 3 && wv == 0)
+                far_part(next, t0 + 4);
+            lds_barrier();
+        }
+    };
+    if (AHEAD == 2) {
+        for (int t0 = 0; t0 < nb; t0 += 8) {
+            round(A, B, t0);
+            round(B, A, t0 + 4);
+        }
+    } else {
+        for (int t0 = 0; t0 < nb; t0 += 4) round(A, A, t0);
+    }
+    __syncthreads();
+}
+
+template <typename T>
+__device__ __forceinline__ void band_back(int n, int kw, const T* Uf, double* b) {
+    if (kw <= 96)
+        band_back_blocked<T, 28, 2>(n, kw, Uf, b);
+    else
+        band_back_blocked<T, 68, 1>(n, kw, Uf, b);
+}
+
+// The workgroup's band solve: forward staged when the stage holds 8 or more
+// steps, otherwise by one wavefront, then backward by blocks.  All threads
+// call it; b is complete for every thread on return.
 template <typename T, int NPL>
 __device__ __forceinline__ void band_solve_group(int n, int kl, int ku, const T* __restrict__ Uf,
                                                  const T* __restrict__ Lf, const int* __restrict__ piv,
                                                  double* b, void* stage, int stage_bytes,
                                                  bool backward_only) {
-    const int G = stage ? band_stage_cols<T, NPL>(stage_bytes) : 0;
-    if (G >= 8) {
-        band_solve_staged<T, NPL>(n, kl, ku, Uf, Lf, piv, b, stage, G, backward_only);
-    } else {
-        if (threadIdx.x < 64) band_solve_wave<T, NPL>(n, kl, ku, Uf, Lf, piv, b, backward_only);
-        __syncthreads();
+    if (!backward_only) {
+        const int G = stage ? band_stage_cols<T, NPL>(stage_bytes) : 0;
+        if (G >= 8) {
+            band_forward_staged<T, NPL>(n, kl, ku, Lf, piv, b, stage, G);
+        } else {
+            if (threadIdx.x < 64) band_solve_wave<T, NPL, true>(n, kl, ku, Uf, Lf, piv, b);
+            __syncthreads();
+        }
     }
+    band_back<T>(n, kl + ku, Uf, b);
 }
 
 // Solve J d = rb in place (rb in LDS).  FP64 factors: one band solve.  FP32
 // factors: iterative refinement with FP64 residuals r0 - J d computed from
 // the FP64 CSR values (columns < n), until ||res|| <= ir_rtol ||r0||.
 // stage (LDS, stage_bytes; may be null): staging space of the band solves.
-template <int NPL>
+template <int NPL, bool MIXED>
 __device__ __forceinline__ void local_linear_solve(const DevMaps& P, const DevLocal& L, const NewtonParams& np,
                                    int i, int n, int rowbase, double* rb, double* r0,
                                    double* dl, double* red, bool forward_done = false,
                                    void* stage = nullptr, int stage_bytes = 0) {
     const int kl = P.kl[i], ku = P.ku[i];
-    const double* Ud = L.Uf + P.off_u[i];
-    const double* Ld = L.Lf + P.off_l[i];
-    const float* Us = np.mixed ? L.Uf32 + P.off_u[i] : nullptr;
-    const float* Ls = np.mixed ? L.Lf32 + P.off_l[i] : nullptr;
     const int* piv = L.piv + rowbase;
-    if (!np.mixed) {
-        band_solve_group<double, NPL>(n, kl, ku, Ud, Ld, piv, rb, stage, stage_bytes, forward_done);
+    if (!MIXED) {
+        band_solve_group<double, NPL>(n, kl, ku, L.Uf + P.off_u[i], L.Lf + P.off_l[i], piv, rb, stage,
+                                      stage_bytes, forward_done);
         return;
     }
+    const float* Us = L.Uf32 + P.off_u[i];
+    const float* Ls = L.Lf32 + P.off_l[i];
     double nr0 = 0.0;
     for (int a = threadIdx.x; a < n; a += blockDim.x) {
         r0[a] = rb[a];
@@ -1455,19 +1906,20 @@ __device__ __forceinline__ void local_linear_solve(const DevMaps& P, const DevLo
     __syncthreads();
 }
 
-// Factor J at the current point into FP64 or FP32 storage.
+// Factor J at the current point into FP64 or (MIXED) FP32 storage.
 // rhs (FP64 only): forward substitution fused with the factorisation.
+template <bool MIXED>
 __device__ __forceinline__ int local_factor(const DevMaps& P, const DevLocal& L, const NewtonParams& np, int i,
-                            int n, int rowbase, void* W, void* mult, int* sflag, bool fp64 = false,
+                            int n, int rowbase, void* W, int wbytes, void* mult, int* sflag,
                             double* rhs = nullptr) {
     const int kl = P.kl[i], ku = P.ku[i];
     const int* rptr = P.jptr + rowbase;
-    if (np.mixed && !fp64)
+    if constexpr (MIXED)
         return band_lu_auto<float>(n, kl, ku, rptr, P.jcol, L.jval, (float*)W, (float*)mult, sflag,
-                              L.Uf32 + P.off_u[i], L.Lf32 + P.off_l[i], L.piv + rowbase, 0,
+                              L.Uf32 + P.off_u[i], L.Lf32 + P.off_l[i], L.piv + rowbase, wbytes, 0,
                               np.lu_variant, nullptr, np.mixed == 2);
     return band_lu_auto<double>(n, kl, ku, rptr, P.jcol, L.jval, (double*)W, (double*)mult, sflag,
-                           L.Uf + P.off_u[i], L.Lf + P.off_l[i], L.piv + rowbase, 0,
+                           L.Uf + P.off_u[i], L.Lf + P.off_l[i], L.piv + rowbase, wbytes, 0,
                            np.lu_variant, rhs);
 }
 
@@ -1481,7 +1933,7 @@ __device__ __forceinline__ int local_factor(const DevMaps& P, const DevLocal& L,
 // Stopping: ||r||_2 <= max(rtol rho_plain, abs_tol sqrt(n_i)) or
 // max|step| <= stagnation max|x|, at most maxit steps.
 // ----------------------------------------------------------------------------
-template <int NPL, bool ELAST>
+template <int NPL, bool ELAST, bool MIXED>
 __global__ void __launch_bounds__(NLS_BLOCK)
 k_local_newton(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* __restrict__ u,
                int lds_bytes) {
@@ -1493,13 +1945,16 @@ k_local_newton(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* 
     const int gbase = P.off_g[i], ng = P.off_g[i + 1] - gbase;
     const int ebase = P.off_e[i];
     const int kl = P.kl[i];
-    double* vp = smem;
-    double* rb = vp + n + ng;
+    // the patch values and the factorisation's window share one region: the
+    // values wait in xstar and ghost while a linear system is solved
+    double* rb = smem;
     double* r0 = rb + n;
-    double* dl = r0 + (np.mixed ? n : 0);
-    double* red = dl + (np.mixed ? n : 0);
+    double* dl = r0 + (MIXED ? n : 0);
+    double* red = dl + (MIXED ? n : 0);
     double* mult = red + 24;
     double* W = mult + ((kl > 1 ? kl : 1) + 1);
+    double* vp = W;
+    const int wbytes = lds_bytes - (int)((char*)W - (char*)smem);
     for (int a = threadIdx.x; a < n; a += blockDim.x) vp[a] = u[P.l2g[rowbase + a]];
     for (int j = threadIdx.x; j < ng; j += blockDim.x) vp[n + j] = u[P.g2g[gbase + j]];
     if (threadIdx.x == 0) sdetf = 0;
@@ -1561,17 +2016,27 @@ k_local_newton(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* 
             }
             if (its == np.maxit) { status = 1; break; }
             local_jacobian<ELAST>(M, P, n, rowbase, ebase, vp, L.jval);
+            // (each thread saves and restores entries of its own)
+            for (int a = threadIdx.x; a < n; a += blockDim.x) L.xstar[rowbase + a] = vp[a];
+            for (int j = threadIdx.x; j < ng; j += blockDim.x) L.ghost[gbase + j] = vp[n + j];
+            auto restore = [&]() {
+                for (int a = threadIdx.x; a < n; a += blockDim.x) vp[a] = L.xstar[rowbase + a];
+                for (int j = threadIdx.x; j < ng; j += blockDim.x) vp[n + j] = L.ghost[gbase + j];
+            };
             __syncthreads();
             // FP64: the factorisation also carries out the forward
             // substitution on the residual, the solve only the backward one
-            if (local_factor(P, L, np, i, n, rowbase, W, mult, sflag, false, np.mixed ? nullptr : rb)) {
+            if (local_factor<MIXED>(P, L, np, i, n, rowbase, W, wbytes, mult, sflag,
+                                    MIXED ? nullptr : rb)) {
                 status = 3;
+                restore();
                 break;
             }
             // the factorisation window is free during the solve: it holds
             // the staged factor columns
-            local_linear_solve<NPL>(P, L, np, i, n, rowbase, rb, r0, dl, red, !np.mixed, W,
-                                    lds_bytes - (int)((char*)W - (char*)smem));
+            local_linear_solve<NPL, MIXED>(P, L, np, i, n, rowbase, rb, r0, dl, red, !MIXED, W,
+                                           wbytes);
+            restore();
             double dm = 0.0;
             for (int a = threadIdx.x; a < n; a += blockDim.x) {
                 vp[a] -= rb[a];
@@ -1587,18 +2052,18 @@ k_local_newton(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* 
         if (status == 0 || start != 1) break;
         start = 2;
     }
-    if (status == 0 && np.keep_factor) {
-        // J and its LU at x*, in FP64, are kept for the exact tangent
-        local_jacobian<ELAST>(M, P, n, rowbase, ebase, vp, L.jval);
-        __syncthreads();
-        if (local_factor(P, L, np, i, n, rowbase, W, mult, sflag, true)) status = 3;
-    }
     for (int a = threadIdx.x; a < n; a += blockDim.x) {
         const int row = rowbase + a;
         L.xstar[row] = vp[a];
         L.T[row] = u[P.l2g[row]] - vp[a];
     }
     for (int j = threadIdx.x; j < ng; j += blockDim.x) L.ghost[gbase + j] = vp[n + j];
+    if (status == 0 && np.keep_factor) {
+        // J and its LU at x*, in FP64, are kept for the exact tangent
+        local_jacobian<ELAST>(M, P, n, rowbase, ebase, vp, L.jval);
+        __syncthreads();
+        if (local_factor<false>(P, L, np, i, n, rowbase, W, wbytes, mult, sflag)) status = 3;
+    }
     if (threadIdx.x == 0) {
         L.its[i] = its;
         L.status[i] = status;
@@ -2447,7 +2912,7 @@ k_coarse_apply_inverse(DevCoarse C, const double* __restrict__ x, double* __rest
 
 // Local part of the exact tangent: z_i = J_ii^{-1} (B_i v_Gamma_i), with J,
 // B at the converged local state (eq. 6 with R_i DF(u_i) v = J R_i v + B v_G).
-template <int NPL>
+template <int NPL, bool MIXED>
 __global__ void __launch_bounds__(NLS_BLOCK)
 k_tangent_local(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* __restrict__ v,
                 int restrict_rhs, int lds_bytes) {
@@ -2457,8 +2922,8 @@ k_tangent_local(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double*
     const int gbase = P.off_g[i];
     double* rb = smem;
     double* r0 = rb + n;
-    double* dl = r0 + (np.mixed ? n : 0);
-    double* red = dl + (np.mixed ? n : 0);
+    double* dl = r0 + (MIXED ? n : 0);
+    double* red = dl + (MIXED ? n : 0);
     for (int a = threadIdx.x; a < n; a += blockDim.x) {
         const int row = rowbase + a;
         double acc = 0.0;
@@ -2474,7 +2939,7 @@ k_tangent_local(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double*
     }
     __syncthreads();
     double* stage = red + 24;
-    local_linear_solve<NPL>(P, L, np, i, n, rowbase, rb, r0, dl, red, false, stage,
+    local_linear_solve<NPL, MIXED>(P, L, np, i, n, rowbase, rb, r0, dl, red, false, stage,
                             lds_bytes - (int)((char*)stage - (char*)smem));
     for (int a = threadIdx.x; a < n; a += blockDim.x) L.z[rowbase + a] = rb[a];
 }
@@ -2586,7 +3051,7 @@ __global__ void __launch_bounds__(NLS_BLOCK) k_coarse_phit(DevCoarse C, const do
 template <bool ELAST>
 __global__ void __launch_bounds__(NLS_BLOCK)
 k_local_factor(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* __restrict__ u,
-               const double* __restrict__ xloc, const double* __restrict__ gloc) {
+               const double* __restrict__ xloc, const double* __restrict__ gloc, int lds_bytes) {
     extern __shared__ double smem[];
     __shared__ int sflag[20];
     const int i = P.order[blockIdx.x];
@@ -2594,13 +3059,9 @@ k_local_factor(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* 
     const int gbase = P.off_g[i], ng = P.off_g[i + 1] - gbase;
     const int ebase = P.off_e[i];
     const int kl = P.kl[i];
-    double* vp = smem;
-    double* rb = vp + n + ng;
-    double* r0 = rb + n;
-    double* dl = r0 + (np.mixed ? n : 0);
-    double* red = dl + (np.mixed ? n : 0);
-    double* mult = red + 24;
+    double* mult = smem;
     double* W = mult + ((kl > 1 ? kl : 1) + 1);
+    double* vp = W;  // needed until the Jacobian is assembled
     for (int a = threadIdx.x; a < n; a += blockDim.x)
         vp[a] = xloc ? xloc[rowbase + a] : u[P.l2g[rowbase + a]];
     for (int j = threadIdx.x; j < ng; j += blockDim.x)
@@ -2608,7 +3069,8 @@ k_local_factor(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* 
     __syncthreads();
     local_jacobian<ELAST>(M, P, n, rowbase, ebase, vp, L.jval);
     __syncthreads();
-    const int status = local_factor(P, L, np, i, n, rowbase, W, mult, sflag, true) ? 3 : 0;
+    const int wbytes = lds_bytes - (int)((char*)W - (char*)smem);
+    const int status = local_factor<false>(P, L, np, i, n, rowbase, W, wbytes, mult, sflag) ? 3 : 0;
     if (threadIdx.x == 0) {
         L.its[i] = 0;
         L.status[i] = status;
@@ -2793,7 +3255,7 @@ __device__ __forceinline__ void coarse_elem_row(const DevMesh& M, const DevCoars
 // = 0 by default (one workgroup per subdomain; setup only).
 template <int NPL, bool ELAST>
 __global__ void __launch_bounds__(NLS_BLOCK)
-k_gdsw_extend(DevMesh M, DevCoarse C, const double* __restrict__ ulin) {
+k_gdsw_extend(DevMesh M, DevCoarse C, const double* __restrict__ ulin, int lds_bytes) {
     constexpr int D = ELAST ? 2 : 1, NV = ELAST ? 4 : 3;
     extern __shared__ double smem[];
     __shared__ int sflag[20];
@@ -2838,7 +3300,8 @@ k_gdsw_extend(DevMesh M, DevCoarse C, const double* __restrict__ ulin) {
     }
     __syncthreads();
     if (band_lu_auto<double>(ni, kl, ku, C.iptr + ib, C.icol, C.ival, W, mult, sflag,
-                        C.iU + C.off_iu[i], C.iL + C.off_il[i], C.ipiv + ib)) {
+                        C.iU + C.off_iu[i], C.iL + C.off_il[i], C.ipiv + ib,
+                        lds_bytes - (int)((char*)W - (char*)smem))) {
         if (threadIdx.x == 0) atomicOr(C.flag, 1);
         return;
     }
@@ -3280,7 +3743,7 @@ k_coarse_lu(DevCoarse C, int factor, int lds_bytes) {
     __syncthreads();
     if (factor) {
         if (band_lu_auto<double>(n, kl, ku, C.a0ptr + off, C.a0col, C.a0val, W, mult, sflag, U, L,
-                                 piv, off, 0, x)) {
+                                 piv, stage_bytes, off, 0, x)) {
             if (threadIdx.x == 0) atomicOr(C.flag, 2);
         }
         __syncthreads();
@@ -3610,14 +4073,18 @@ hipError_t launch_local_newton(const DevMesh& M, const DevMaps& P, const DevLoca
                                const NewtonParams& np, const double* u, int nblk, int lds_bytes,
                                int npl, hipStream_t s) {
     hipError_t e;
-#define NLS_LN(NPL, EL)                                                              \
-    e = set_lds(k_local_newton<NPL, EL>, lds_bytes);                                 \
+#define NLS_LN(NPL, EL, MX)                                                          \
+    e = set_lds(k_local_newton<NPL, EL, MX>, lds_bytes);                             \
     if (e != hipSuccess) return e;                                                   \
-    k_local_newton<NPL, EL><<<nblk, NLS_BLOCK, lds_bytes, s>>>(M, P, L, np, u, lds_bytes);
+    k_local_newton<NPL, EL, MX><<<nblk, NLS_BLOCK, lds_bytes, s>>>(M, P, L, np, u, lds_bytes);
+    // in FP64 the factorisation carries out the forward substitution, so only
+    // the mixed form depends on the band's values per lane
     if (M.kind == NLS_PROBLEM_NEOHOOKE) {
-        if (npl <= 1) { NLS_LN(1, true) } else if (npl == 2) { NLS_LN(2, true) } else { NLS_LN(4, true) }
+        if (!np.mixed) { NLS_LN(1, true, false) }
+        else if (npl <= 1) { NLS_LN(1, true, true) } else if (npl == 2) { NLS_LN(2, true, true) } else { NLS_LN(4, true, true) }
     } else {
-        if (npl <= 1) { NLS_LN(1, false) } else if (npl == 2) { NLS_LN(2, false) } else { NLS_LN(4, false) }
+        if (!np.mixed) { NLS_LN(1, false, false) }
+        else if (npl <= 1) { NLS_LN(1, false, true) } else if (npl == 2) { NLS_LN(2, false, true) } else { NLS_LN(4, false, true) }
     }
 #undef NLS_LN
     return hipGetLastError();
@@ -3646,11 +4113,15 @@ hipError_t launch_tangent_local(const DevMesh& M, const DevMaps& P, const DevLoc
                                 const NewtonParams& np, const double* v, int lds_bytes, int npl,
                                 hipStream_t s, int restrict_rhs) {
     hipError_t e;
-#define NLS_TL(NPL)                                                                  \
-    e = set_lds(k_tangent_local<NPL>, lds_bytes);                                    \
+#define NLS_TL(NPL, MX)                                                              \
+    e = set_lds(k_tangent_local<NPL, MX>, lds_bytes);                                \
     if (e != hipSuccess) return e;                                                   \
-    k_tangent_local<NPL><<<P.nsub, NLS_BLOCK, lds_bytes, s>>>(M, P, L, np, v, restrict_rhs, lds_bytes);
-    if (npl <= 1) { NLS_TL(1) } else if (npl == 2) { NLS_TL(2) } else { NLS_TL(4) }
+    k_tangent_local<NPL, MX><<<P.nsub, NLS_BLOCK, lds_bytes, s>>>(M, P, L, np, v, restrict_rhs, lds_bytes);
+    if (np.mixed) {
+        if (npl <= 1) { NLS_TL(1, true) } else if (npl == 2) { NLS_TL(2, true) } else { NLS_TL(4, true) }
+    } else {
+        if (npl <= 1) { NLS_TL(1, false) } else if (npl == 2) { NLS_TL(2, false) } else { NLS_TL(4, false) }
+    }
 #undef NLS_TL
     return hipGetLastError();
 }
@@ -3685,11 +4156,13 @@ hipError_t launch_local_factor(const DevMesh& M, const DevMaps& P, const DevLoca
     if (M.kind == NLS_PROBLEM_NEOHOOKE) {
         e = set_lds(k_local_factor<true>, lds_bytes);
         if (e != hipSuccess) return e;
-        k_local_factor<true><<<nblk, NLS_BLOCK, lds_bytes, s>>>(M, P, L, np, u, xloc, gloc);
+        k_local_factor<true><<<nblk, NLS_BLOCK, lds_bytes, s>>>(M, P, L, np, u, xloc, gloc,
+                                                                     lds_bytes);
     } else {
         e = set_lds(k_local_factor<false>, lds_bytes);
         if (e != hipSuccess) return e;
-        k_local_factor<false><<<nblk, NLS_BLOCK, lds_bytes, s>>>(M, P, L, np, u, xloc, gloc);
+        k_local_factor<false><<<nblk, NLS_BLOCK, lds_bytes, s>>>(M, P, L, np, u, xloc, gloc,
+                                                                     lds_bytes);
     }
     return hipGetLastError();
 }
@@ -3706,7 +4179,7 @@ hipError_t launch_gdsw_extend(const DevMesh& M, const DevCoarse& C, const double
 #define NLS_GE(NPL, EL)                                                              \
     e = set_lds(k_gdsw_extend<NPL, EL>, lds_bytes);                                  \
     if (e != hipSuccess) return e;                                                   \
-    k_gdsw_extend<NPL, EL><<<C.nsub, NLS_BLOCK, lds_bytes, s>>>(M, C, ulin);
+    k_gdsw_extend<NPL, EL><<<C.nsub, NLS_BLOCK, lds_bytes, s>>>(M, C, ulin, lds_bytes);
     if (M.kind == NLS_PROBLEM_NEOHOOKE) {
         if (npl <= 1) { NLS_GE(1, true) } else if (npl == 2) { NLS_GE(2, true) } else { NLS_GE(4, true) }
     } else {

@@ -132,6 +132,15 @@ struct DevCoarse {
     int* flag;                  // [0] zero pivot in the coarse/interior LU
 };
 
+// Working storage of the regrouped band LU (band_lu_gauss) in bytes: two
+// windows of 16 + kl rows by gauss_ld columns, G and two panels by columns,
+// and the panel's permutation.
+#define NLS_GAUSS_LG 80
+static inline __host__ __device__ int gauss_ld(int kl, int ku) { return (16 + (kl + ku + 15) / 16 * 16) | 1; }
+static inline __host__ __device__ int gauss_window_bytes(int kl, int ku, int elem) {
+    return (2 * (16 + kl) * gauss_ld(kl, ku) + 16 * NLS_GAUSS_LG + 32 * 64) * elem + 64 * 4;
+}
+
 // ---- launchers (kernels.hip) ------------------------------------------------
 hipError_t launch_p1_setup(const DevMesh& M, const double* xy, const double* elem_coef,
                            const double* elem_load, double* G6, double* kappa,
