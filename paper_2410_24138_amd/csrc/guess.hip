@@ -245,88 +245,194 @@ k_guess_target(DevGuessTables T, const double* __restrict__ u, const double* __r
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int GBM = 64, GBN = 64, GBK = 32, GLD = GBK + 8;
+constexpr int GBM = 32, GBN = 64, GBK = 64, GLD = GBK + 8;
 
-// 64 x 64 output tile per workgroup of four waves; each wave owns a 32 x 32
-// quarter as 2 x 2 blocks of the 16x16x16 bf16 MFMA.  A and B tiles are
-// staged in LDS with k contiguous, so every lane reads its 4 consecutive k
-// values of one row of A and one column of B.  Ragged edges read zeros.
-__global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
-    __shared__ uint16_t As[GBM * GLD];
-    __shared__ uint16_t Bs[GBN * GLD];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int wm = w >> 1, wn = w & 1;
-    const int m0 = blockIdx.y * GBM, n0 = blockIdx.x * GBN;
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int lr = lane & 15, lk = 4 * (lane >> 4);
-    for (int k0 = 0; k0 < g.K; k0 += GBK) {
-        for (int e = tid; e < GBM * GBK; e += 256) {
-            const int mm = e / GBK, kk = e % GBK;
-            const int gm = m0 + mm, gk = k0 + kk;
-            As[mm * GLD + kk] = (gm < g.M && gk < g.K) ? g.A[gm * g.sam + gk * g.sak] : (uint16_t)0;
+// A tile of ROWS rows by GBK values of k in registers and in LDS (k
+// contiguous, pitch GLD).  KC: k is contiguous in memory (element (r, k) at
+// p[r ld + k]), else r is (p[k ld + r]); 16-byte loads either way, eight
+// values that the second form writes down the tile's rows.  Rows and k values
+// past their ends are zeros; along the contiguous direction the sizes are
+// multiples of 8 (320, 256) and the bases 16-byte aligned.
+template <int ROWS, bool KC>
+struct Stage {
+    static constexpr int NCH = ROWS * GBK / 8 / 256;
+    uint4 v[NCH];
+    __device__ __forceinline__ void place(int c, int& r, int& k) const {
+        const int e = threadIdx.x + 256 * c;
+        if (KC) {
+            r = e / (GBK / 8);
+            k = 8 * (e % (GBK / 8));
+        } else {
+            k = e / (ROWS / 8);
+            r = 8 * (e % (ROWS / 8));
         }
-        for (int e = tid; e < GBN * GBK; e += 256) {
-            const int nn = e % GBN, kk = e / GBN;
-            const int gn = n0 + nn, gk = k0 + kk;
-            Bs[nn * GLD + kk] = (gn < g.N && gk < g.K) ? g.B[gk * g.sbk + gn * g.sbn] : (uint16_t)0;
+    }
+    __device__ __forceinline__ void load(const uint16_t* __restrict__ p, int ld, int r0, int rows,
+                                         int k0, int kend) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            int r, k;
+            place(c, r, k);
+            r += r0;
+            k += k0;
+            v[c] = uint4{0, 0, 0, 0};
+            if (r < rows && k < kend)
+                v[c] = *(const uint4*)(p + (KC ? (size_t)r * ld + k : (size_t)k * ld + r));
         }
+    }
+    __device__ __forceinline__ void store(uint16_t* T) const {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            int r, k;
+            place(c, r, k);
+            if (KC) {
+                *(uint4*)(T + r * GLD + k) = v[c];
+            } else {
+                const uint32_t w[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    T[(r + i) * GLD + k] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
+            }
+        }
+    }
+};
+
+// A 32 x 64 output tile by four wavefronts of 16 x 32 (two blocks of the
+// 16x16x16 bf16 matrix-core step, k ascending).  The next 64 values of k are
+// fetched into registers while the current ones are multiplied.
+template <bool AK, bool BK>
+__device__ __forceinline__ void gemm_tile(const uint16_t* __restrict__ A, int lda, int M,
+                                          const uint16_t* __restrict__ B, int ldb, int N, int m0,
+                                          int n0, int kbeg, int kend, uint16_t* As, uint16_t* Bs,
+                                          f32x4 (&acc)[2]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int wm = w >> 1, wn = w & 1, lr = lane & 15, lk = 4 * (lane >> 4);
+    acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Stage<GBM, AK> a;
+    Stage<GBN, BK> b;
+    a.load(A, lda, m0, M, kbeg, kend);
+    b.load(B, ldb, n0, N, kbeg, kend);
+    for (int k0 = kbeg; k0 < kend; k0 += GBK) {
+        a.store(As);
+        b.store(Bs);
         __syncthreads();
+        if (k0 + GBK < kend) {
+            a.load(A, lda, m0, M, k0 + GBK, kend);
+            b.load(B, ldb, n0, N, k0 + GBK, kend);
+        }
 #pragma unroll
         for (int kk = 0; kk < GBK; kk += 16) {
-            bf16x4 av[2], bv[2];
+            const bf16x4 av = *(const bf16x4*)&As[(wm * 16 + lr) * GLD + kk + lk];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const uint16_t* pa = &As[(wm * 32 + t * 16 + lr) * GLD + kk + lk];
-                const uint16_t* pb = &Bs[(wn * 32 + t * 16 + lr) * GLD + kk + lk];
-                av[t] = bf16x4{(short)pa[0], (short)pa[1], (short)pa[2], (short)pa[3]};
-                bv[t] = bf16x4{(short)pb[0], (short)pb[1], (short)pb[2], (short)pb[3]};
+                const bf16x4 bv = *(const bf16x4*)&Bs[(wn * 32 + t * 16 + lr) * GLD + kk + lk];
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc[t], 0, 0, 0);
             }
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av[a], bv[b], acc[a][b], 0, 0, 0);
         }
         __syncthreads();
     }
+}
+
+// The layers' products.  Bound by launch and load latency at the sizes of a
+// batch (1,280 rows: 160 tiles and 5 k-steps; 7 us per layer, 26 us with 64 x
+// 64 tiles staged element by element).
+template <bool AK, bool BK>
+__global__ void __launch_bounds__(256) k_gemm_bf16(GemmArgs g) {
+    __shared__ __align__(16) uint16_t As[GBM * GLD];
+    __shared__ __align__(16) uint16_t Bs[GBN * GLD];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int m0 = blockIdx.y * GBM, n0 = blockIdx.x * GBN;
+    f32x4 acc[2];
+    gemm_tile<AK, BK>(g.A, g.lda, g.M, g.B, g.ldb, g.N, m0, n0, 0, g.K, As, Bs, acc);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int row = m0 + wm * 32 + a * 16 + lk + j;
-                const int col = n0 + wn * 32 + b * 16 + lr;
-                if (row >= g.M || col >= g.N) continue;
-                const float v = acc[a][b][j];
-                switch (g.epi) {
-                case EPI_STORE:
-                    g.out[(size_t)row * g.ldo + col] = v;
-                    break;
-                case EPI_BIAS_GELU: {
-                    const float z = v + g.bias[col];
-                    if (g.out) g.out[(size_t)row * g.ldo + col] = z;
-                    g.outb[(size_t)row * g.ldob + col] = f2bf(gelu(z));
-                    break;
-                }
-                case EPI_BIAS: {
-                    float z = v + g.bias[col];
-                    if (g.oscale) z = z * g.oscale[col] + g.oshift[col];
-                    g.out[(size_t)row * g.ldo + col] = z;
-                    break;
-                }
-                default: {
-                    const float d = v * gelu_prime(g.aux[(size_t)row * g.ldaux + col]);
-                    g.out[(size_t)row * g.ldo + col] = d;
-                    g.outb[(size_t)row * g.ldob + col] = f2bf(d);
-                    break;
-                }
-                }
+        for (int j = 0; j < 4; ++j) {
+            const int row = m0 + (w >> 1) * 16 + 4 * (lane >> 4) + j;
+            const int col = n0 + (w & 1) * 32 + t * 16 + (lane & 15);
+            if (row >= g.M || col >= g.N) continue;
+            const float v = acc[t][j];
+            switch (g.epi) {
+            case EPI_BIAS_GELU: {
+                const float z = v + g.bias[col];
+                if (g.out) g.out[(size_t)row * g.ldo + col] = z;
+                g.outb[(size_t)row * g.ldob + col] = f2bf(gelu(z));
+                break;
             }
+            case EPI_BIAS: {
+                float z = v + g.bias[col];
+                if (g.oscale) z = z * g.oscale[col] + g.oshift[col];
+                g.out[(size_t)row * g.ldo + col] = z;
+                break;
+            }
+            default: {
+                const float d = v * gelu_prime(g.aux[(size_t)row * g.ldaux + col]);
+                g.out[(size_t)row * g.ldo + col] = d;
+                g.outb[(size_t)row * g.ldob + col] = f2bf(d);
+                break;
+            }
+            }
+        }
+}
+
+// Weight and bias gradients of all layers, the rows of the batch split over
+// blockIdx.y: block x forms one 32 x 64 tile of dW_l = dZ_l^T X_l, or (the last
+// blocks of a layer) 64 column sums of dZ_l, of its rows, into split y of the
+// partial sums; k_grad_sum adds the splits in order.  (1,280 rows: 952 blocks
+// in one launch, 14 us; four products of 20 blocks and four column sums of one
+// block took 4 x 147 and 4 x 293 us.)
+__global__ void __launch_bounds__(256) k_grad_partial(GradArgs g) {
+    __shared__ __align__(16) uint16_t As[GBM * GLD];
+    __shared__ __align__(16) uint16_t Bs[GBN * GLD];
+    int l = 0;
+    while (l + 1 < 4 && (int)blockIdx.x >= g.first[l + 1]) ++l;
+    const int q = blockIdx.x - g.first[l], in = g.in[l];
+    const int r0 = blockIdx.y * g.chunk, r1 = min(g.rows, r0 + g.chunk);
+    float* out = g.part + (size_t)blockIdx.y * g.nparam;
+    const int nt = in / GBN, ntile = nt * (NLS_G_WIDTH / GBM);
+    if (q >= ntile) {
+        // column sums: 16 rows at a time, 16 columns per four threads' rows
+        __shared__ float red[256];
+        const int c = 64 * (q - ntile) + (threadIdx.x & 63), part = threadIdx.x >> 6;
+        float s = 0.f;
+        const float* dz = g.dz[l] + c;
+        int r = r0 + part;
+        for (; r + 28 < r1; r += 32) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = dz[(size_t)(r + 4 * u) * NLS_G_WIDTH];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; r < r1; r += 4) s += dz[(size_t)r * NLS_G_WIDTH];
+        red[threadIdx.x] = s;
+        __syncthreads();
+        if (part == 0)
+            out[g.off_b[l] + c] = (red[threadIdx.x] + red[threadIdx.x + 64]) +
+                                  (red[threadIdx.x + 128] + red[threadIdx.x + 192]);
+        return;
+    }
+    const int m0 = GBM * (q / nt), n0 = GBN * (q % nt);
+    f32x4 acc[2];
+    gemm_tile<false, false>(g.dzb[l], NLS_G_WIDTH, NLS_G_WIDTH, g.x[l], in, in, m0, n0, r0, r1, As,
+                            Bs, acc);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int row = m0 + (w >> 1) * 16 + 4 * (lane >> 4) + j;
+            const int col = n0 + (w & 1) * 32 + t * 16 + (lane & 15);
+            out[g.off_w[l] + (size_t)row * in + col] = acc[t][j];
+        }
+}
+
+__global__ void k_grad_sum(const float* __restrict__ part, int splits, int n, float* __restrict__ grad) {
+    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    float s = part[p];
+    for (int y = 1; y < splits; ++y) s += part[(size_t)y * n + p];
+    grad[p] = s;
 }
 
 // ------------------------------------------------------------- training
@@ -398,19 +504,13 @@ k_mse_grad(const float* __restrict__ Y, const float* __restrict__ Tn, int64_t to
 
 __global__ void k_mse_final(const double* __restrict__ partial, int nb, double inv_total,
                             double* __restrict__ loss_acc) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    // one wavefront: each lane its share, then a fixed tree
     double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += partial[b];
+    for (int b = threadIdx.x; b < nb; b += 64) s += partial[b];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    if (threadIdx.x != 0) return;
     loss_acc[0] += s * inv_total;
     loss_acc[1] += 1.0;
-}
-
-__global__ void k_colsum(const float* __restrict__ dz, int rows, int cols, float* __restrict__ out) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= cols) return;
-    float s = 0.f;
-    for (int r = 0; r < rows; ++r) s += dz[(size_t)r * cols + c];
-    out[c] = s;
 }
 
 // Adam (Kingma and Ba) with bias corrections c1 = 1/(1-b1^t),
@@ -485,7 +585,28 @@ hipError_t launch_check_indices(const int* idx, int64_t n, int64_t limit, int* f
 hipError_t launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
     if (g.M <= 0 || g.N <= 0) return hipSuccess;
     dim3 grid((g.N + GBN - 1) / GBN, (g.M + GBM - 1) / GBM);
-    k_gemm_bf16<<<grid, 256, 0, s>>>(g);
+    if (g.bk)
+        k_gemm_bf16<true, true><<<grid, 256, 0, s>>>(g);
+    else
+        k_gemm_bf16<true, false><<<grid, 256, 0, s>>>(g);
+    return hipGetLastError();
+}
+
+hipError_t launch_grad(GradArgs g, float* grad, hipStream_t s) {
+    if (g.rows <= 0) return hipSuccess;
+    // whole k-steps per split, at most NLS_G_SPLITS of them
+    g.chunk = (g.rows + NLS_G_SPLITS - 1) / NLS_G_SPLITS;
+    g.chunk = (g.chunk + GBK - 1) / GBK * GBK;
+    const int splits = (g.rows + g.chunk - 1) / g.chunk;
+    int blocks = 0;
+    for (int l = 0; l < 4; ++l) {
+        g.first[l] = blocks;
+        blocks += (g.in[l] / GBN) * (NLS_G_WIDTH / GBM) + NLS_G_WIDTH / 64;
+    }
+    k_grad_partial<<<dim3(blocks, splits), 256, 0, s>>>(g);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_grad_sum<<<(g.nparam + 255) / 256, 256, 0, s>>>(g.part, splits, g.nparam, grad);
     return hipGetLastError();
 }
 
@@ -553,12 +674,6 @@ hipError_t launch_mse_grad(const float* Y, const float* Tn, int rows, float* dz,
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_mse_final<<<1, 64, 0, s>>>(partial, nb, 1.0 / (double)total, loss_acc);
-    return hipGetLastError();
-}
-
-hipError_t launch_colsum(const float* dz, int rows, int cols, float* out, hipStream_t s) {
-    if (cols <= 0) return hipSuccess;
-    k_colsum<<<(cols + 255) / 256, 256, 0, s>>>(dz, rows, cols, out);
     return hipGetLastError();
 }
 

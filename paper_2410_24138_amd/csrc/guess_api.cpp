@@ -37,6 +37,7 @@ struct GuessState {
     int64_t t = 0;
     double* lacc = nullptr;   // [sum of step losses, steps]
     double* part = nullptr;   // 256 partial sums
+    float* gpart = nullptr;   // partial sums of the gradient
     int* counts = nullptr;    // start statistics
     // inference over the subdomains
     int inf_rows = 0;
@@ -54,9 +55,9 @@ struct GuessState {
     int64_t cap = 0, count = 0;
     // batch buffers (training and test hooks)
     int tb = 0;
-    uint16_t *tx = nullptr, *ta[3] = {nullptr, nullptr, nullptr}, *dzb[2] = {nullptr, nullptr};
+    uint16_t *tx = nullptr, *ta[3] = {nullptr, nullptr, nullptr}, *dzb[4] = {};
     float *tz[3] = {nullptr, nullptr, nullptr}, *ty = nullptr, *ttn = nullptr,
-          *dz[2] = {nullptr, nullptr};
+          *dz[4] = {};
 
     void free_group(int gi) {
         for (void* p : bufs[gi]) (void)hipFree(p);
@@ -154,7 +155,7 @@ static int ensure_batch(nls_handle* h, int rows) {
         RC(galloc(h, GuessState::B_BATCH, &g->ta[l], r * NLS_G_WIDTH));
         RC(galloc(h, GuessState::B_BATCH, &g->tz[l], r * NLS_G_WIDTH));
     }
-    for (int l = 0; l < 2; ++l) {
+    for (int l = 0; l < 4; ++l) {
         RC(galloc(h, GuessState::B_BATCH, &g->dz[l], r * NLS_G_WIDTH));
         RC(galloc(h, GuessState::B_BATCH, &g->dzb[l], r * NLS_G_WIDTH));
     }
@@ -177,11 +178,10 @@ static int forward(nls_handle* h, const uint16_t* x0, int rows, float* const* z,
         ga.N = NLS_G_WIDTH;
         ga.K = in;
         ga.A = l == 0 ? x0 : a[l - 1];
-        ga.sam = in;
-        ga.sak = 1;
+        ga.lda = in;
         ga.B = g->wb + OFF_W[l];
-        ga.sbk = 1;
-        ga.sbn = in;
+        ga.ldb = in;
+        ga.bk = true;
         ga.bias = g->w + OFF_B[l];
         if (l < 3) {
             ga.epi = EPI_BIAS_GELU;
@@ -207,47 +207,39 @@ static int forward(nls_handle* h, const uint16_t* x0, int rows, float* const* z,
 // g->grad; the step loss is added to lacc.
 static int backward(nls_handle* h, const uint16_t* x0, int rows) {
     GuessState* g = h->guess;
-    HIPCHK(launch_mse_grad(g->ty, g->ttn, rows, g->dz[0], g->dzb[0], g->part, g->lacc, h->stream));
-    int cur = 0;
+    HIPCHK(launch_mse_grad(g->ty, g->ttn, rows, g->dz[3], g->dzb[3], g->part, g->lacc, h->stream));
+    GradArgs gw{};
+    gw.rows = rows;
+    gw.nparam = NLS_G_NPARAM;
+    gw.part = g->gpart;
     for (int l = 3; l >= 0; --l) {
-        const int in = l == 0 ? NLS_G_IN : NLS_G_WIDTH;
-        GemmArgs gw{};
-        gw.M = NLS_G_WIDTH;
-        gw.N = in;
-        gw.K = rows;
-        gw.A = g->dzb[cur];
-        gw.sam = 1;
-        gw.sak = NLS_G_WIDTH;
-        gw.B = l == 0 ? x0 : g->ta[l - 1];
-        gw.sbk = in;
-        gw.sbn = 1;
-        gw.epi = EPI_STORE;
-        gw.out = g->grad + OFF_W[l];
-        gw.ldo = in;
-        HIPCHK(launch_gemm_bf16(gw, h->stream));
-        HIPCHK(launch_colsum(g->dz[cur], rows, NLS_G_WIDTH, g->grad + OFF_B[l], h->stream));
+        gw.in[l] = l == 0 ? NLS_G_IN : NLS_G_WIDTH;
+        gw.off_w[l] = OFF_W[l];
+        gw.off_b[l] = OFF_B[l];
+        gw.x[l] = l == 0 ? x0 : g->ta[l - 1];
+        gw.dz[l] = g->dz[l];
+        gw.dzb[l] = g->dzb[l];
         if (l > 0) {
             GemmArgs gd{};
             gd.M = rows;
             gd.N = NLS_G_WIDTH;
             gd.K = NLS_G_WIDTH;
-            gd.A = g->dzb[cur];
-            gd.sam = NLS_G_WIDTH;
-            gd.sak = 1;
+            gd.A = g->dzb[l];
+            gd.lda = NLS_G_WIDTH;
             gd.B = g->wb + OFF_W[l];
-            gd.sbk = NLS_G_WIDTH;
-            gd.sbn = 1;
+            gd.ldb = NLS_G_WIDTH;
+            gd.bk = false;
             gd.epi = EPI_GELU_BWD;
             gd.aux = g->tz[l - 1];
             gd.ldaux = NLS_G_WIDTH;
-            gd.out = g->dz[1 - cur];
+            gd.out = g->dz[l - 1];
             gd.ldo = NLS_G_WIDTH;
-            gd.outb = g->dzb[1 - cur];
+            gd.outb = g->dzb[l - 1];
             gd.ldob = NLS_G_WIDTH;
             HIPCHK(launch_gemm_bf16(gd, h->stream));
-            cur = 1 - cur;
         }
     }
+    HIPCHK(launch_grad(gw, g->grad, h->stream));
     return NLS_OK;
 }
 
@@ -368,6 +360,7 @@ extern "C" int nls_guess_set_model(nls_handle* h, const float* params, int64_t n
         RC(galloc(h, GuessState::B_MODEL, &g->norm, NORM_FLOATS));
         RC(galloc(h, GuessState::B_MODEL, &g->lacc, 2));
         RC(galloc(h, GuessState::B_MODEL, &g->part, 256));
+        RC(galloc(h, GuessState::B_MODEL, &g->gpart, (size_t)NLS_G_SPLITS * NLS_G_NPARAM));
         RC(galloc(h, GuessState::B_MODEL, &g->counts, 2));
     }
     HIPCHK(hipMemcpyAsync(g->w, params, NLS_G_NPARAM * sizeof(float), hipMemcpyHostToDevice, h->stream));

@@ -52,20 +52,22 @@ struct DevGuessTables {
 };
 
 enum GemmEpilogue {
-    EPI_STORE = 0,      // out = acc
     EPI_BIAS_GELU = 1,  // z = acc + bias; out = z; outb = bf16(gelu(z))
     EPI_BIAS = 2,       // z = acc + bias; out = z, or z * oscale + oshift
     EPI_GELU_BWD = 3,   // d = acc * gelu'(aux); out = d; outb = bf16(d)
 };
 
-// C[M x N] = A[M x K] B[K x N], bfloat16 operands addressed through
-// strides (element (m,k) of A at A[m*sam + k*sak]), FP32 accumulation.
+// C[M x N] = A[M x K] B[K x N], bfloat16 operands, FP32 accumulation: A with
+// k contiguous (element (m, k) at A[m*lda + k]), B with k contiguous where bk
+// (B[n*ldb + k]), else with n contiguous (B[k*ldb + n]).  Sizes along the
+// contiguous directions are multiples of 8, bases 16-byte aligned.
 struct GemmArgs {
     int M, N, K;
     const uint16_t* A;
-    long sam, sak;
+    int lda;
     const uint16_t* B;
-    long sbk, sbn;
+    int ldb;
+    bool bk;
     int epi;
     const float* bias;
     float* out;
@@ -94,7 +96,19 @@ hipError_t launch_gather_batch(const float* X, const float* T, const int* idx, i
                                const float* norm, uint16_t* xb, float* tn, hipStream_t s);
 hipError_t launch_mse_grad(const float* Y, const float* Tn, int rows, float* dz, uint16_t* dzb,
                            double* partial, double* loss_acc, hipStream_t s);
-hipError_t launch_colsum(const float* dz, int rows, int cols, float* out, hipStream_t s);
+// Gradients of all layers from the layers' inputs x (bfloat16, rows x in) and
+// output gradients dz (FP32) and dzb (bfloat16), rows x 256, into grad (weights
+// at off_w, biases at off_b); part: NLS_G_SPLITS x nparam partial sums.
+#define NLS_G_SPLITS 8
+struct GradArgs {
+    int rows, nparam;
+    int in[4], off_w[4], off_b[4];
+    const uint16_t *x[4], *dzb[4];
+    const float* dz[4];
+    float* part;
+    int chunk, first[4];  // set by the launcher
+};
+hipError_t launch_grad(GradArgs g, float* grad, hipStream_t s);
 hipError_t launch_adam(float* w, const float* g, float* m, float* v, uint16_t* wb, int64_t n,
                        float lr, float b1, float b2, float eps, float c1, float c2,
                        hipStream_t s);
