@@ -726,6 +726,14 @@ extern "C" int nls_build_coarse(nls_handle* h, int kind, const double* u_lin) {
     RC(h->alloc(G_COARSE, &d.a0U, (size_t)C.offU.back() + 1024));
     RC(h->alloc(G_COARSE, &d.a0L, (size_t)C.offL.back() + 1024));
     RC(h->alloc(G_COARSE, &d.a0piv, C.n0));
+    // bands too wide for one row per lane of the panel (kl > 48) and for an LDS
+    // window, up to two rows per lane
+    d.win = nullptr;
+    if (C.a0kl > 48 && C.a0kl <= 112 && maxb * 8 + wide_lds_bytes() <= kLdsGrowCap) {
+        d.win_stride = 2 * (16 + C.a0kl) * gauss_ld(C.a0kl, C.a0ku) + 64;
+        d.win_lds = maxb * 8 + wide_lds_bytes();
+        RC(h->alloc(G_COARSE, &d.win, C.bkl.size() * (size_t)d.win_stride));
+    }
     RC(h->alloc(G_COARSE, &d.rhs, C.n0));
     RC(h->alloc(G_COARSE, &d.c, C.n0));
     RC(h->alloc(G_COARSE, &d.w, h->mesh.ndof()));

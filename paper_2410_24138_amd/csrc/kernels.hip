@@ -544,6 +544,17 @@ __device__ __forceinline__ unsigned dpp_umax(unsigned v) {
     return max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWMASK, 0xf, false));
 }
 
+// Largest key of the wavefront.
+__device__ __forceinline__ unsigned wave_umax(unsigned key) {
+    key = dpp_umax<0xB1, 0xf>(key);   // quad_perm [1,0,3,2]
+    key = dpp_umax<0x4E, 0xf>(key);   // quad_perm [2,3,0,1]
+    key = dpp_umax<0x141, 0xf>(key);  // row_half_mirror
+    key = dpp_umax<0x140, 0xf>(key);  // row_mirror
+    key = dpp_umax<0x142, 0xa>(key);  // row_bcast:15 into rows 1, 3
+    key = dpp_umax<0x143, 0xc>(key);  // row_bcast:31 into rows 2, 3
+    return (unsigned)__builtin_amdgcn_readlane((int)key, 63);
+}
+
 // Index (0..63) of an entry of largest |a| over the wavefront (a < 0 marks
 // lanes that do not take part), compared on the high word of |a| with its 6
 // low bits replaced by 63 - idx: entries within a relative 2^-14 of each
@@ -552,14 +563,7 @@ __device__ __forceinline__ unsigned dpp_umax(unsigned v) {
 __device__ __forceinline__ int wave_argmax_hi(double a, int idx) {
     unsigned key = 0u;
     if (a >= 0.0) key = ((unsigned)__double2hiint(a) & ~63u) | (unsigned)(63 - idx);
-    key = dpp_umax<0xB1, 0xf>(key);   // quad_perm [1,0,3,2]
-    key = dpp_umax<0x4E, 0xf>(key);   // quad_perm [2,3,0,1]
-    key = dpp_umax<0x141, 0xf>(key);  // row_half_mirror
-    key = dpp_umax<0x140, 0xf>(key);  // row_mirror
-    key = dpp_umax<0x142, 0xa>(key);  // row_bcast:15 into rows 1, 3
-    key = dpp_umax<0x143, 0xc>(key);  // row_bcast:31 into rows 2, 3
-    key = (unsigned)__builtin_amdgcn_readlane((int)key, 63);
-    return 63 - (int)(key & 63u);
+    return 63 - (int)(wave_umax(key) & 63u);
 }
 
 // One 16x16x4 matrix-core step D = A B + C: A is 16 x 4 with lane l holding
@@ -1367,6 +1371,381 @@ __device__ __forceinline__ int band_lu_gauss(int n_, int kl_, int ku_, const int
         }
     }
     __syncthreads();  // factors in HBM are complete for the workgroup
+    return sh[0];
+}
+
+// ----------------------------------------------------------------------------
+// The same factorisation for bands of kl <= 112 on one workgroup of 8
+// wavefronts (the coarse matrix of an elasticity problem): two window rows per
+// lane in the panel, the two windows in global memory (win; 0.3 MB at kl = 90,
+// which stays in L2), but their first 16 columns, which only the panel reads,
+// in LDS.  Wavefront 0 runs the panels; wavefront 1 forms and stores U12 and
+// the panel's columns, wavefronts 2-7 the rows below, 2-5 the entering rows.
+// 434 rows, kl = 87: 0.3 ms with the solve (2.65 ms by band_lu, a barrier per
+// column).
+// ----------------------------------------------------------------------------
+constexpr int WIDE_THREADS = 512;
+__device__ __forceinline__ int band_lu_wide(int n_, int kl_, int ku_, const int* __restrict__ rptr_,
+                                            const int* __restrict__ cols_,
+                                            const double* __restrict__ vals_, double* win, double* lds,
+                                            int* sh, double* __restrict__ Uf, double* __restrict__ Lf,
+                                            int* __restrict__ piv_, int cbase, double* rhs) {
+    constexpr int NB = 16, LG = NLS_WIDE_LG, LP = 128, LC = 17, MID = 7;
+    typedef Mfma<double>::acc_t acc_t;
+    const int n = uniform(n_), kl = uniform(kl_), ku = uniform(ku_);
+    const int* __restrict__ rptr = uniform(rptr_);
+    const int* __restrict__ cols = uniform(cols_);
+    const double* __restrict__ vals = uniform(vals_);
+    int* __restrict__ piv = uniform(piv_);
+    const int tid = threadIdx.x, lane = tid & 63, wv = uniform(tid >> 6);
+    const int H = NB + kl, ld = gauss_ld(kl, ku), kw = kl + ku, ldu = kw + 1, ldl = kl > 1 ? kl : 1;
+    double* Wa = uniform(win);   // the window of the current panel, columns 16 ..
+    double* Wb = Wa + H * ld;    // the next one
+    double* Ca = lds;            // columns 0 .. 15 of the current window
+    double* Cb = Ca + LP * LC;   // and of the next one
+    double* Gs = Cb + LP * LC;   // G by columns
+    double* Ps = Gs + NB * LG;   // the factored panel by columns (two copies)
+    int* sig = (int*)(Ps + 2 * NB * LP);
+    for (int e = tid; e < 2 * H * ld; e += WIDE_THREADS) Wa[e] = 0.0;
+    for (int e = tid; e < 2 * LP * LC; e += WIDE_THREADS) Ca[e] = 0.0;
+    if (tid == 0) sh[0] = 0;
+    __syncthreads();
+    // entry (row r of the window, column c) of the window in (W, C)
+    auto put = [&](double* W, double* C, int r, int c, double v) {
+        if (c < NB)
+            C[r * LC + c] = v;
+        else
+            W[r * ld + c] = v;
+    };
+    for (int r = tid >> 2, q = tid & 3; r < H; r += WIDE_THREADS / 4) {
+        if (r < n) {
+            for (int s = rptr[r] + q; s < rptr[r + 1]; s += 4) {
+                const int c = cols[s] - cbase;
+                if (c < n) put(Wa, Ca, r, c, vals[s]);
+            }
+        } else if (q == 0) {
+            put(Wa, Ca, r, r, 1.0);
+        }
+    }
+    // entering rows: lane 16 sl + t of wavefront 2 + w holds slots t, t + 16, ..
+    // of entering row 4 w + sl
+    constexpr int LPR = 16, RPW = 4, PF = 4;
+    const int et = lane & (LPR - 1), eq = RPW * (wv - 2) + lane / LPR;
+    const bool enter = wv >= 2 && wv < 6;
+    int rs1 = 0, re1 = 0, rs2 = 0, re2 = 0;
+    int ec[PF];
+    double ev[PF];
+    auto load_ptr = [&](int k0, int& rs, int& re) {
+        const int r = k0 + H + eq;
+        rs = enter && r < n ? rptr[r] : 0;
+        re = enter && r < n ? rptr[r + 1] : 0;
+    };
+    auto load_ent = [&](int rs, int re) {
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            const int s = rs + et + LPR * u;
+            ec[u] = -1;
+            ev[u] = 0.0;
+            if (s < re) {
+                ec[u] = cols[s] - cbase;
+                ev[u] = vals[s];
+            }
+        }
+    };
+    const int li = lane & 15, lk = lane >> 4;
+    const int nrt = (H + 15) >> 4, nct = (kw + 15) >> 4;
+    const __amdgpu_buffer_rsrc_t Lr = store_range(Lf, (unsigned)(n * ldl) * sizeof(double));
+    const __amdgpu_buffer_rsrc_t Ur = store_range(Uf, (unsigned)(n * ldu) * sizeof(double));
+    // two column tiles from ct of row tile rt (see band_lu_gauss); tile 0 goes
+    // to the next window's LDS columns
+    auto tiles = [&](auto top, auto cts, int k0, const double* src, double* dst, double* dstc, int rt,
+                     int ct, int cb) {
+        constexpr bool TOP = decltype(top)::value;
+        constexpr int CT = decltype(cts)::value;
+        double ga[4], bv[CT][4];
+        acc_t acc[CT];
+        int sb[4];
+        const int r = 16 * rt + li;
+        const double* w = src + NB + 16 * ct;
+        const double* c = w + __umul24(sig[r], ld) + Mfma<double>::row(lk, 0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            sb[s] = __umul24(sig[4 * s + lk], ld);
+            ga[s] = Gs[(4 * s + lk) * LG + r];
+        }
+#pragma unroll
+        for (int u = 0; u < CT; ++u) {
+            const int o = ct + u < cb ? 16 * u : 0;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                bv[u][s] = w[sb[s] + o + li];
+                acc[u][s] = TOP ? 0.0 : c[o + Mfma<double>::row(0, s)];
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int u = 0; u < CT; ++u) acc[u] = Mfma<double>::step(bv[u][s], ga[s], acc[u]);
+        if (TOP) {
+#pragma unroll
+            for (int u = 0; u < CT; ++u)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const int t = 16 * (ct + u) + Mfma<double>::row(lk, s), o = NB + t - li;
+                    range_store(Ur, ct + u < cb && o <= kw ? ((k0 + NB + t) * ldu + o) * 8u : kNoStore,
+                                acc[u][s]);
+                }
+        } else if (r < H) {
+#pragma unroll
+            for (int u = 0; u < CT; ++u) {
+                if (ct + u >= cb) continue;
+                const int t = 16 * (ct + u) + Mfma<double>::row(lk, 0);
+                if (ct + u == 0) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        dstc[(r - NB) * LC + t + Mfma<double>::row(0, s)] = acc[u][s];
+                } else {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        dst[(r - NB) * ld + t + Mfma<double>::row(0, s)] = acc[u][s];
+                }
+            }
+        }
+    };
+    typedef std::integral_constant<bool, true> Top;
+    typedef std::integral_constant<bool, false> Below;
+    typedef std::integral_constant<int, 1> One;
+    typedef std::integral_constant<int, 2> Two;
+    const int npair = nct >> 1;  // column tiles 1 .. in pairs
+    auto rhs_update = [&](int k0) {
+        double x[2], y[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int q = lane + 64 * h, r = sig[q];
+            x[h] = k0 + r < n ? rhs[k0 + r] : 0.0;
+            y[h] = q < NB ? 0.0 : x[h];
+        }
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const double xk = rdlane(x[0], k);
+            y[0] += Gs[k * LG + lane] * xk;
+            y[1] += Gs[k * LG + lane + 64] * xk;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int q = lane + 64 * h;
+            if (q < H && k0 + q < n) rhs[k0 + q] = y[h];
+        }
+    };
+    auto panel_out = [&](int k0) {
+#pragma unroll 4
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int q = lane + 64 * h;
+                const double v = Ps[(k0 & NB) * LP + j * LP + q];
+                const unsigned ou = j - q, ol = q - j - 1;
+                if (h == 0)
+                    range_store(Ur, ou <= (unsigned)kw ? ((k0 + j) * ldu + ou) * 8u : kNoStore, v);
+                range_store(Lr, ol < (unsigned)kl ? ((k0 + j) * ldl + ol) * 8u : kNoStore, v);
+            }
+    };
+    auto swap = [&]() {
+        double* t = Wa;
+        Wa = Wb;
+        Wb = t;
+        t = Ca;
+        Ca = Cb;
+        Cb = t;
+    };
+    __syncthreads();
+    if (wv == 0) {
+        bool search = false;
+        for (int k0 = 0; k0 < n; k0 += NB) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            const bool have[2] = {ln < H, ln + 64 < H};
+            double* const Pk = Ps + (k0 & NB) * LP;
+            double p[2][NB], g[2][NB];
+            auto load = [&]() {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int c = 0; c < NB; ++c) {
+                        const double w = Ca[(ln + 64 * h) * LC + c];
+                        p[h][c] = have[h] ? w : 0.0;
+                    }
+            };
+            load();
+            int pos[2] = {ln, ln + 64}, dsel = ln;
+            bool redo = search;
+            if (!search) {
+                double lmax = 0.0, pmin = fabs(rdlane(p[0][0], 0));
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    const double pv = rdlane(p[0][j], j);
+                    double pr[NB];
+#pragma unroll
+                    for (int c = 0; c < NB; ++c)
+                        if (c != j) pr[c] = rdlane(c > j ? p[0][c] : g[0][c], j);
+                    const double inv = recip(pv);
+                    const double l0 = p[0][j] * inv, l1 = p[1][j] * inv;
+                    const double l = ln > j ? l0 : 0.0;
+                    p[0][j] = ln > j ? l0 : p[0][j];
+                    p[1][j] = l1;
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int c = j + 1; c < NB; ++c) {
+                        p[0][c] -= l * pr[c];
+                        p[1][c] -= l1 * pr[c];
+                    }
+#pragma unroll
+                    for (int c = 0; c < j; ++c) {
+                        g[0][c] -= l * pr[c];
+                        g[1][c] -= l1 * pr[c];
+                    }
+                    g[0][j] = ln == j ? 1.0 : -l;
+                    g[1][j] = -l1;
+                    lmax = fmax(lmax, fmax(fabs(l), fabs(l1)));
+                    pmin = fmin(pmin, fabs(pv));
+                    if (j == MID) __syncthreads();
+                }
+                redo = __ballot(lmax > 1.0 + 0x1p-13) != 0 || pmin == 0.0;
+            }
+            if (!redo) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    Pk[j * LP + ln] = p[0][j];
+                    Pk[j * LP + ln + 64] = p[1][j];
+                }
+            } else {
+                if (search)
+                    __syncthreads();
+                else
+                    load();
+                int sing = 0;
+                bool used[2] = {false, false};
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    double av[2];
+                    bool cand[2];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        cand[h] = have[h] && !used[h];
+                        av[h] = fabs(p[h][j]);
+                    }
+                    const unsigned long long b0 = __ballot(have[0] && pos[0] == j),
+                                             b1 = __ballot(have[1] && pos[1] == j);
+                    int hp = b0 == 0, pl = __ffsll(b0 ? b0 : b1) - 1, d = j;
+                    const double aj = fabs(rdlane(hp ? p[1][j] : p[0][j], pl));
+                    if (__ballot((cand[0] && av[0] > aj) || (cand[1] && av[1] > aj)) != 0) {
+                        unsigned key = 0u;
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const double a = av[h] <= DBL_MAX ? av[h] : DBL_MAX;
+                            const unsigned kh =
+                                ((unsigned)__double2hiint(a) & ~127u) | (unsigned)(127 - pos[h]);
+                            key = max(key, cand[h] ? kh : 0u);
+                        }
+                        d = 127 - (int)(wave_umax(key) & 127u);
+                        const unsigned long long c0 = __ballot(cand[0] && pos[0] == d),
+                                                 c1 = __ballot(cand[1] && pos[1] == d);
+                        hp = c0 == 0;
+                        pl = __ffsll(c0 ? c0 : c1) - 1;
+                    }
+                    dsel = ln == j ? d : dsel;
+                    const double pv = rdlane(hp ? p[1][j] : p[0][j], pl);
+                    sing |= pv == 0.0 ? 1 : 0;
+                    const double inv = pv != 0.0 ? recip(pv) : 0.0;
+                    double l[2];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const bool me = ln == pl && h == hp;
+                        pos[h] = pos[h] == j ? d : (me ? j : pos[h]);
+                        l[h] = cand[h] && !me ? p[h][j] * inv : 0.0;
+                        used[h] = used[h] || me;
+                        Pk[j * LP + pos[h]] = cand[h] && !me ? l[h] : p[h][j];
+                    }
+#pragma unroll
+                    for (int c = 0; c < NB; ++c) {
+                        if (c == j) continue;
+                        const double v = c > j ? (hp ? p[1][c] : p[0][c]) : (hp ? g[1][c] : g[0][c]);
+                        const double prc = rdlane(v, pl);
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            if (c > j)
+                                p[h][c] -= l[h] * prc;
+                            else
+                                g[h][c] -= l[h] * prc;
+                        }
+                    }
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) g[h][j] = ln == pl && h == hp ? 1.0 : -l[h];
+                }
+                search = __ballot((have[0] && pos[0] != ln) || (have[1] && pos[1] != ln + 64)) != 0;
+                if (ln == 0 && sing) sh[0] = 1;
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int c = 0; c < NB; ++c) Gs[c * LG + pos[h]] = g[h][c];
+                sig[pos[h]] = have[h] ? ln + 64 * h : 0;
+            }
+            __syncthreads();
+            if (ln < NB && k0 + ln < n) piv[k0 + ln] = k0 + dsel;
+            tiles(Top(), One(), k0, Wa, Wb, Cb, 0, 0, 1);
+            __syncthreads();
+            swap();
+        }
+    } else {
+        load_ptr(0, rs1, re1);
+        load_ent(rs1, re1);
+        load_ptr(NB, rs2, re2);
+        for (int k0 = 0; k0 < n; k0 += NB) {
+            const int k1 = k0 + NB;
+            if (k0 > 0) {
+                if (wv == 1) {
+                    for (int i = 0; i < npair; ++i)
+                        tiles(Top(), Two(), k0 - NB, Wb, Wa, Ca, 0, 1 + 2 * i, nct);
+                } else {
+                    if (rhs && wv == 7) rhs_update(k0 - NB);
+                    for (int i = wv - 2; i < (nrt - 1) * npair; i += 6) {
+                        const int pair = i / (nrt - 1), rt = 1 + i - pair * (nrt - 1);
+                        tiles(Below(), Two(), k0 - NB, Wb, Wa, Ca, rt, 1 + 2 * pair, nct);
+                    }
+                }
+            }
+            __syncthreads();
+            if (wv == 1 && k0 > 0) panel_out(k0 - NB);
+            if (wv >= 6)  // the columns that enter in the rows that stay
+                for (int r = lk + 4 * (wv - 6); r < kl; r += 8) Wb[r * ld + 16 * nct + li] = 0.0;
+            if (enter) {
+                double* const E = Wb + (kl + RPW * (wv - 2)) * ld;
+                for (int c = lane; c < RPW * ld; c += 64) E[c] = 0.0;
+                for (int c = lane; c < RPW * LC; c += 64) Cb[(kl + RPW * (wv - 2)) * LC + c] = 0.0;
+#pragma unroll
+                for (int u = 0; u < PF; ++u)
+                    if (ec[u] >= 0 && ec[u] < n) put(Wb, Cb, kl + eq, ec[u] - k1, ev[u]);
+                if (et == 0 && k0 + H + eq >= n) put(Wb, Cb, kl + eq, kl + eq, 1.0);
+                for (int s = rs1 + et + PF * LPR; s < re1; s += LPR) {
+                    const int c = cols[s] - cbase;
+                    if (c < n) put(Wb, Cb, kl + eq, c - k1, vals[s]);
+                }
+                rs1 = rs2;
+                re1 = re2;
+                load_ent(rs1, re1);
+                load_ptr(k1 + NB, rs2, re2);
+            }
+            __syncthreads();
+            if (wv < nrt) tiles(Below(), One(), k0, Wa, Wb, Cb, wv, 0, 1);
+            __syncthreads();
+            swap();
+        }
+        const int kl0 = (n - 1) / NB * NB;
+        if (wv == 1 && n > 0) panel_out(kl0);
+        if (rhs && wv == 7 && n > 0) rhs_update(kl0);
+    }
+    __syncthreads();
     return sh[0];
 }
 
@@ -3753,6 +4132,26 @@ k_coarse_lu(DevCoarse C, int factor, int lds_bytes) {
     for (int k = threadIdx.x; k < n; k += blockDim.x) C.rhs[off + k] = x[k];
 }
 
+// Factor A0 and solve A0 d = rhs in place, as k_coarse_lu, for bands of 48 <
+// kl <= 112 (k_coarse_lu's panel has one row per lane).
+__global__ void __launch_bounds__(WIDE_THREADS) k_coarse_lu_wide(DevCoarse C) {
+    extern __shared__ double smem[];
+    __shared__ int sflag[4];
+    const int b = blockIdx.x;
+    const int off = C.boff[b], n = C.boff[b + 1] - off, kl = C.bkl[b], ku = C.bku[b];
+    double* x = smem;
+    double* U = C.a0U + C.offU[b];
+    for (int k = threadIdx.x; k < n; k += blockDim.x) x[k] = C.rhs[off + k];
+    __syncthreads();
+    if (band_lu_wide(n, kl, ku, C.a0ptr + off, C.a0col, C.a0val, C.win + (size_t)b * C.win_stride,
+                     smem + n, sflag, U, C.a0L + C.offL[b], C.a0piv + off, off, x)) {
+        if (threadIdx.x == 0) atomicOr(C.flag, 2);
+    }
+    __syncthreads();
+    band_back<double>(n, kl + ku, U, x);
+    for (int k = threadIdx.x; k < n; k += blockDim.x) C.rhs[off + k] = x[k];
+}
+
 // c += d (d in band order); scal[1] = max|d|, scal[2] = max|c| (new c).
 __global__ void __launch_bounds__(NLS_BLOCK) k_coarse_update(DevCoarse C) {
     __shared__ double red[24];
@@ -4240,6 +4639,12 @@ hipError_t launch_coarse_assemble(const DevCoarse& C, int with_matrix, hipStream
 
 hipError_t launch_coarse_lu(const DevCoarse& C, int factor, int lds_bytes, int npl, hipStream_t s) {
     hipError_t e;
+    if (factor && C.win) {
+        e = set_lds(k_coarse_lu_wide, C.win_lds);
+        if (e != hipSuccess) return e;
+        k_coarse_lu_wide<<<C.nblk, WIDE_THREADS, C.win_lds, s>>>(C);
+        return hipGetLastError();
+    }
 #define NLS_CL(NPL)                                                                  \
     e = set_lds(k_coarse_lu<NPL>, lds_bytes);                                        \
     if (e != hipSuccess) return e;                                                   \

@@ -126,6 +126,10 @@ struct DevCoarse {
     int inv_nblk, inv_nkk;
     int* inv_sig;
     double *inv_G, *inv_Ui, *inv_Y;
+    // windows of the factorisation of a wide band (48 < kl <= 112), win_stride
+    // entries per diagonal block, and the LDS bytes of its kernel; else null
+    double* win;
+    int win_stride, win_lds;
     double* c;                  // n0, coarse iterate (coarse id order)
     double* w;                  // N: u - Phi c
     double* scal;               // device scalars: [0] ||G||, [1] max|dc|, [2] max|c|
@@ -139,6 +143,13 @@ struct DevCoarse {
 static inline __host__ __device__ int gauss_ld(int kl, int ku) { return (16 + (kl + ku + 15) / 16 * 16) | 1; }
 static inline __host__ __device__ int gauss_window_bytes(int kl, int ku, int elem) {
     return (2 * (16 + kl) * gauss_ld(kl, ku) + 16 * NLS_GAUSS_LG + 32 * 64) * elem + 64 * 4;
+}
+
+// LDS of the wide band LU (band_lu_wide) in bytes: 16 columns of two windows
+// of up to 128 rows, G and two panels by columns, and the permutation.
+#define NLS_WIDE_LG 144
+static inline __host__ __device__ int wide_lds_bytes() {
+    return (2 * 128 * 17 + 16 * NLS_WIDE_LG + 2 * 16 * 128) * 8 + 128 * 4;
 }
 
 // ---- launchers (kernels.hip) ------------------------------------------------
