@@ -4132,8 +4132,9 @@ k_coarse_lu(DevCoarse C, int factor, int lds_bytes) {
     for (int k = threadIdx.x; k < n; k += blockDim.x) C.rhs[off + k] = x[k];
 }
 
-// Factor A0 and solve A0 d = rhs in place, as k_coarse_lu, for bands of 48 <
-// kl <= 112 (k_coarse_lu's panel has one row per lane).
+// Factor A0 and forward substitute rhs in place, for bands of 48 < kl <= 112
+// (k_coarse_lu's panel has one row per lane); k_coarse_back ends the solve, in
+// a launch of its own: its blocks need the registers of four wavefronts.
 __global__ void __launch_bounds__(WIDE_THREADS) k_coarse_lu_wide(DevCoarse C) {
     extern __shared__ double smem[];
     __shared__ int sflag[4];
@@ -4148,8 +4149,17 @@ __global__ void __launch_bounds__(WIDE_THREADS) k_coarse_lu_wide(DevCoarse C) {
         if (threadIdx.x == 0) atomicOr(C.flag, 2);
     }
     __syncthreads();
-    band_back<double>(n, kl + ku, U, x);
     for (int k = threadIdx.x; k < n; k += blockDim.x) C.rhs[off + k] = x[k];
+}
+
+__global__ void __launch_bounds__(NLS_BLOCK) k_coarse_back(DevCoarse C) {
+    extern __shared__ double smem[];
+    const int b = blockIdx.x;
+    const int off = C.boff[b], n = C.boff[b + 1] - off;
+    for (int k = threadIdx.x; k < n; k += blockDim.x) smem[k] = C.rhs[off + k];
+    __syncthreads();
+    band_back<double>(n, C.bkl[b] + C.bku[b], C.a0U + C.offU[b], smem);
+    for (int k = threadIdx.x; k < n; k += blockDim.x) C.rhs[off + k] = smem[k];
 }
 
 // c += d (d in band order); scal[1] = max|d|, scal[2] = max|c| (new c).
@@ -4643,6 +4653,12 @@ hipError_t launch_coarse_lu(const DevCoarse& C, int factor, int lds_bytes, int n
         e = set_lds(k_coarse_lu_wide, C.win_lds);
         if (e != hipSuccess) return e;
         k_coarse_lu_wide<<<C.nblk, WIDE_THREADS, C.win_lds, s>>>(C);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const int back_lds = C.win_lds - wide_lds_bytes();  // one right-hand side
+        e = set_lds(k_coarse_back, back_lds);
+        if (e != hipSuccess) return e;
+        k_coarse_back<<<C.nblk, NLS_BLOCK, back_lds, s>>>(C);
         return hipGetLastError();
     }
 #define NLS_CL(NPL)                                                                  \
