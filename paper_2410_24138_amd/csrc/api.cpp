@@ -9,7 +9,7 @@
 //   tangent  y = v + sum_i P~_i J_ii^{-1} B_i v_Gi + Phi A0^{-1} Phi^T DF(u_0) v
 //            (eqs. 6, 7, 12, using R_i DF(u_i) v = J_ii R_i v + B_i v_Gi);
 //   GMRES    restarted, classical Gram-Schmidt with one reorthogonalisation,
-//            Givens rotations on the host (a few scalars per iteration);
+//            Givens rotations on the device;
 //   Newton   u <- u - du (eq. 13).
 #include <hip/hip_runtime.h>
 
@@ -1433,7 +1433,7 @@ static int arnoldi_step(nls_handle* h, int j, hipStream_t s) {
     const int64_t ld = N;
     double* vj = h->V + (int64_t)j * ld;
     double* vn = h->V + (int64_t)(j + 1) * ld;
-    RC(tangent(h, vj, h->wv, s));
+    RC(tangent(h, vj, h->wv, s == h->stream ? nullptr : s));
     // norm partial sums after the (m + 1) nb dot-product partials
     double* pnorm = h->partial + (int64_t)h->nb_dot * (h->m + 1);
     HIPCHK(launch_arnoldi_gs(h->V, ld, j + 1, h->wv, N, h->partial, pnorm, h->hbuf, h->hbuf2,
@@ -1474,12 +1474,53 @@ static int block_graph(nls_handle* h, int b, hipGraphExec_t* out) {
     return NLS_OK;
 }
 
-// Restarted GMRES as gmres() below, with the Hessenberg rotations on the
-// device and each block of gblock Arnoldi steps replayed as one graph; the
-// host reads the convergence state once per block.  Steps of a block after
-// convergence run but are not used.
-static int gmres_graph(nls_handle* h, const double* b, double* x, int* its_out) {
-    RC(prepare_tangent(h));
+// Steps j, j + 1, .. of a cycle one by one on the handle's stream, at most
+// `budget` of them, until one meets the tolerance: *used counts them (up to
+// the one that met it), *conv tells whether one did.  The host reads a step's
+// state while the next step is already enqueued, so the device does not wait
+// for it; a step that turns out not to be needed leaves the state alone.
+// Where a step solves band systems (no explicit tangent blocks) it costs more
+// than that wait, and nothing is enqueued ahead.
+static int gmres_steps(nls_handle* h, int budget, int* used, int* conv) {
+    const int ahead = (h->tangent_w && !h->nks_mode) ? 2 : 1;
+    for (hipEvent_t& e : h->sev)
+        if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    const int last = std::min(h->m, budget);
+    int issued = 0, done = 0;
+    *conv = 0;
+    while (done < last) {
+        while (issued < last && issued - done < ahead) {
+            RC(arnoldi_step(h, issued, h->stream));
+            HIPCHK(hipMemcpyAsync(pin_graph(h) + 2 * (issued & 1), h->gst, 2 * sizeof(int),
+                                  hipMemcpyDeviceToHost, h->stream));
+            HIPCHK(hipEventRecord(h->sev[issued & 1], h->stream));
+            ++issued;
+        }
+        HIPCHK(hipEventSynchronize(h->sev[done & 1]));
+        const int st = pin_graph(h)[2 * (done & 1)];
+        ++done;
+        if (st < 0) {
+            RC(sync(h));
+            return fail(h, NLS_ENAN, "GMRES breakdown (non-finite)");
+        }
+        if (st > 0) {
+            *conv = 1;
+            done = st;
+            break;
+        }
+    }
+    *used = done;
+    return NLS_OK;
+}
+
+// Restarted GMRES(m) for D F_x(u) x = b from x = 0 (classical Gram-Schmidt
+// with one reorthogonalisation, Hessenberg rotations on the device).  Returns
+// the iteration count in *its_out.  graph: blocks of gblock Arnoldi steps are
+// replayed as one graph each and the host reads the convergence state once
+// per block; steps of a block after convergence run but are not used.
+// Otherwise the steps are enqueued one by one.
+static int gmres(nls_handle* h, const double* b, double* x, int* its_out, bool graph) {
+    if (!h->nks_mode) RC(prepare_tangent(h));
     const int N = h->mesh.ndof(), m = h->m, K = h->gblock;
     double bn2 = 0.0;
     RC(dot_host(h, b, b, N, &bn2));
@@ -1487,11 +1528,12 @@ static int gmres_graph(nls_handle* h, const double* b, double* x, int* its_out) 
     HIPCHK(hipMemsetAsync(x, 0, sizeof(double) * N, h->stream));
     *its_out = 0;
     if (bn == 0.0) return NLS_OK;
-    if (!h->gstream) {
+    if (graph && !h->gstream) {
         HIPCHK(hipStreamCreateWithFlags(&h->gstream, hipStreamNonBlocking));
         HIPCHK(hipEventCreateWithFlags(&h->gev[0], hipEventDisableTiming));
         HIPCHK(hipEventCreateWithFlags(&h->gev[1], hipEventDisableTiming));
     }
+    const hipStream_t gs = graph ? h->gstream : h->stream;
     const double tol = h->opt.gmres_rtol * bn;
     HIPCHK(hipMemcpyAsync(h->gtol, &tol, sizeof(double), hipMemcpyHostToDevice, h->stream));
     std::vector<double> H((size_t)(m + 1) * m), g(m + 1), y(m), g0(m + 1);
@@ -1518,132 +1560,54 @@ static int gmres_graph(nls_handle* h, const double* b, double* x, int* its_out) 
         const int st0[2] = {0, 0};
         HIPCHK(hipMemcpyAsync(h->gd, g0.data(), (m + 1) * sizeof(double), hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->gst, st0, sizeof(st0), hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipEventRecord(h->gev[0], h->stream));
-        HIPCHK(hipStreamWaitEvent(h->gstream, h->gev[0], 0));
         int j = 0, conv = 0;
-        while (j < m) {
-            const int budget = h->opt.gmres_maxit - its - j;
-            if (budget <= 0) break;
-            const int blk = j / K, jn = std::min((blk + 1) * K, m);
-            if (j == blk * K && jn - j <= budget) {
-                hipGraphExec_t ex = nullptr;
-                RC(block_graph(h, blk, &ex));
-                HIPCHK(hipGraphLaunch(ex, h->gstream));
-            } else {
-                for (int jj = j; jj < std::min(jn, j + budget); ++jj) RC(arnoldi_step(h, jj, h->gstream));
+        if (!graph) {
+            RC(gmres_steps(h, h->opt.gmres_maxit - its, &j, &conv));
+        } else {
+            HIPCHK(hipEventRecord(h->gev[0], h->stream));
+            HIPCHK(hipStreamWaitEvent(h->gstream, h->gev[0], 0));
+            while (j < m) {
+                const int budget = h->opt.gmres_maxit - its - j;
+                if (budget <= 0) break;
+                const int blk = j / K, jn = std::min((blk + 1) * K, m);
+                if (j == blk * K && jn - j <= budget) {
+                    hipGraphExec_t ex = nullptr;
+                    RC(block_graph(h, blk, &ex));
+                    HIPCHK(hipGraphLaunch(ex, h->gstream));
+                } else {
+                    for (int jj = j; jj < std::min(jn, j + budget); ++jj) RC(arnoldi_step(h, jj, h->gstream));
+                }
+                HIPCHK(hipMemcpyAsync(pin_graph(h), h->gst, 2 * sizeof(int), hipMemcpyDeviceToHost,
+                                      h->gstream));
+                HIPCHK(hipStreamSynchronize(h->gstream));
+                const int st[2] = {pin_graph(h)[0], pin_graph(h)[1]};
+                if (st[0] < 0) return fail(h, NLS_ENAN, "GMRES breakdown (non-finite)");
+                if (st[0] > 0) {
+                    conv = st[0];
+                    j = conv;
+                    break;
+                }
+                j = st[1];
             }
-            HIPCHK(hipMemcpyAsync(pin_graph(h), h->gst, 2 * sizeof(int), hipMemcpyDeviceToHost,
-                                  h->gstream));
-            HIPCHK(hipStreamSynchronize(h->gstream));
-            const int st[2] = {pin_graph(h)[0], pin_graph(h)[1]};
-            if (st[0] < 0) return fail(h, NLS_ENAN, "GMRES breakdown (non-finite)");
-            if (st[0] > 0) {
-                conv = st[0];
-                j = conv;
-                break;
-            }
-            j = st[1];
         }
         if (j == 0) break;
-        HIPCHK(hipMemcpyAsync(H.data(), h->Hd, H.size() * sizeof(double), hipMemcpyDeviceToHost, h->gstream));
-        HIPCHK(hipMemcpyAsync(g.data(), h->gd, (m + 1) * sizeof(double), hipMemcpyDeviceToHost, h->gstream));
-        HIPCHK(hipStreamSynchronize(h->gstream));
+        HIPCHK(hipMemcpyAsync(H.data(), h->Hd, H.size() * sizeof(double), hipMemcpyDeviceToHost, gs));
+        HIPCHK(hipMemcpyAsync(g.data(), h->gd, (m + 1) * sizeof(double), hipMemcpyDeviceToHost, gs));
+        HIPCHK(hipStreamSynchronize(gs));
         for (int i = j - 1; i >= 0; --i) {
             double s = g[i];
             for (int k = i + 1; k < j; ++k) s -= H[(size_t)i * m + k] * y[k];
             y[i] = s / H[(size_t)i * m + i];
         }
-        HIPCHK(hipMemcpyAsync(h->ydev, y.data(), j * sizeof(double), hipMemcpyHostToDevice, h->gstream));
-        HIPCHK(launch_maxpy(h->V, N, j, h->ydev, x, N, -1.0, h->gstream));
-        HIPCHK(hipEventRecord(h->gev[1], h->gstream));
-        HIPCHK(hipStreamWaitEvent(h->stream, h->gev[1], 0));
+        HIPCHK(hipMemcpyAsync(h->ydev, y.data(), j * sizeof(double), hipMemcpyHostToDevice, gs));
+        HIPCHK(launch_maxpy(h->V, N, j, h->ydev, x, N, -1.0, gs));
+        if (graph) {
+            HIPCHK(hipEventRecord(h->gev[1], h->gstream));
+            HIPCHK(hipStreamWaitEvent(h->stream, h->gev[1], 0));
+        }
         its += j;
         RC(sync(h));
         if (conv) break;
-    }
-    *its_out = its;
-    return NLS_OK;
-}
-
-// Restarted GMRES(m) for D F_x(u) x = b from x = 0 (classical Gram-Schmidt
-// with one reorthogonalisation).  Returns the iteration count in *its.
-static int gmres(nls_handle* h, const double* b, double* x, int* its_out) {
-    if (!h->nks_mode) RC(prepare_tangent(h));
-    const int N = h->mesh.ndof(), m = h->m;
-    const int64_t ld = N;
-    double bn2 = 0.0;
-    RC(dot_host(h, b, b, N, &bn2));
-    const double bn = std::sqrt(bn2);
-    HIPCHK(hipMemsetAsync(x, 0, sizeof(double) * N, h->stream));
-    int its = 0;
-    *its_out = 0;
-    if (bn == 0.0) return NLS_OK;
-    const double rtol = h->opt.gmres_rtol;
-    std::vector<double> H((m + 1) * m, 0.0), cs(m), sn(m), g(m + 1), hh(m + 2), hh2(m + 2), y(m);
-    bool first = true;
-    while (its < h->opt.gmres_maxit) {
-        double beta2;
-        if (first) {
-            HIPCHK(hipMemcpyAsync(h->V, b, sizeof(double) * N, hipMemcpyDeviceToDevice, h->stream));
-            beta2 = bn2;
-        } else {
-            RC(tangent(h, x, h->tmp));
-            HIPCHK(hipMemcpyAsync(h->V, b, sizeof(double) * N, hipMemcpyDeviceToDevice, h->stream));
-            HIPCHK(launch_axpy(-1.0, h->tmp, h->V, N, h->stream));
-            RC(dot_host(h, h->V, h->V, N, &beta2));
-        }
-        first = false;
-        const double beta = std::sqrt(beta2);
-        if (beta <= rtol * bn) break;
-        HIPCHK(hipMemcpyAsync(h->hn2, &beta2, sizeof(double), hipMemcpyHostToDevice, h->stream));
-        HIPCHK(launch_scale_by(h->V, h->hn2, h->V, N, h->stream));
-        std::fill(g.begin(), g.end(), 0.0);
-        g[0] = beta;
-        int j = 0;
-        bool done = false;
-        while (j < m && its < h->opt.gmres_maxit) {
-            double* vj = h->V + (int64_t)j * ld;
-            double* vn = h->V + (int64_t)(j + 1) * ld;
-            RC(tangent(h, vj, h->wv));
-            ++its;
-            HIPCHK(launch_mdot(h->V, ld, j + 1, h->wv, N, h->partial, h->hbuf, h->nb_dot, h->stream));
-            HIPCHK(launch_maxpy(h->V, ld, j + 1, h->hbuf, h->wv, N, 1.0, h->stream));
-            HIPCHK(launch_mdot(h->V, ld, j + 1, h->wv, N, h->partial, h->hbuf2, h->nb_dot, h->stream));
-            HIPCHK(launch_maxpy_norm(h->V, ld, j + 1, h->hbuf2, h->wv, N, h->partial, h->hn2,
-                                     h->nb_dot, h->stream));
-            HIPCHK(launch_scale_by(h->wv, h->hn2, vn, N, h->stream));
-            double hn2;
-            HIPCHK(hipMemcpyAsync(hh.data(), h->hbuf, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-            HIPCHK(hipMemcpyAsync(hh2.data(), h->hbuf2, (j + 1) * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-            HIPCHK(hipMemcpyAsync(&hn2, h->hn2, sizeof(double), hipMemcpyDeviceToHost, h->stream));
-            RC(sync(h));
-            for (int i = 0; i <= j; ++i) H[i * m + j] = hh[i] + hh2[i];
-            H[(j + 1) * m + j] = std::sqrt(hn2);
-            for (int i = 0; i < j; ++i) {
-                const double t = cs[i] * H[i * m + j] + sn[i] * H[(i + 1) * m + j];
-                H[(i + 1) * m + j] = -sn[i] * H[i * m + j] + cs[i] * H[(i + 1) * m + j];
-                H[i * m + j] = t;
-            }
-            const double den = std::hypot(H[j * m + j], H[(j + 1) * m + j]);
-            cs[j] = den > 0.0 ? H[j * m + j] / den : 1.0;
-            sn[j] = den > 0.0 ? H[(j + 1) * m + j] / den : 0.0;
-            H[j * m + j] = den;
-            H[(j + 1) * m + j] = 0.0;
-            g[j + 1] = -sn[j] * g[j];
-            g[j] = cs[j] * g[j];
-            ++j;
-            if (!std::isfinite(g[j])) return fail(h, NLS_ENAN, "GMRES breakdown (non-finite)");
-            if (std::fabs(g[j]) <= rtol * bn) { done = true; break; }
-        }
-        for (int i = j - 1; i >= 0; --i) {
-            double s = g[i];
-            for (int k = i + 1; k < j; ++k) s -= H[i * m + k] * y[k];
-            y[i] = s / H[i * m + i];
-        }
-        HIPCHK(hipMemcpyAsync(h->ydev, y.data(), j * sizeof(double), hipMemcpyHostToDevice, h->stream));
-        HIPCHK(launch_maxpy(h->V, ld, j, h->ydev, x, N, -1.0, h->stream));
-        RC(sync(h));
-        if (done) break;
     }
     *its_out = its;
     return NLS_OK;
@@ -1744,7 +1708,7 @@ static int solve_impl(nls_handle* h, double* u, int u_on_device, nls_stats* st) 
         if (rc) return finish(rc);
         Timer tg;
         int gits = 0;
-        rc = graph_gmres_ok(h) ? gmres_graph(h, h->Fx, h->du, &gits) : gmres(h, h->Fx, h->du, &gits);
+        rc = gmres(h, h->Fx, h->du, &gits, graph_gmres_ok(h));
         S->ms_gmres += tg.ms();
         if (rc) return finish(rc);
         S->gmres_its[k] = gits;
@@ -1949,7 +1913,7 @@ extern "C" int nls_solve_nks(nls_handle* h, double* u, int u_on_device, nls_stat
         Timer tg;
         int gits = 0;
         h->nks_mode = true;
-        rc = gmres(h, h->Fx, h->du, &gits);  // right-preconditioned: du holds y
+        rc = gmres(h, h->Fx, h->du, &gits, false);  // right-preconditioned: du holds y
         if (rc == NLS_OK) rc = nks_precond(h, h->du, h->stream) ? NLS_EHIP : NLS_OK;
         h->nks_mode = false;
         S->ms_gmres += tg.ms();

@@ -107,6 +107,7 @@ struct nls_handle {
     std::vector<hipEvent_t> bev;
     hipEvent_t cev[4] = {nullptr, nullptr, nullptr, nullptr};
     hipEvent_t gev[2] = {nullptr, nullptr};
+    hipEvent_t sev[2] = {nullptr, nullptr};  // steps enqueued one by one
     std::vector<hipGraphExec_t> gexec;
     double *Hd = nullptr, *csd = nullptr, *snd = nullptr, *gd = nullptr, *gtol = nullptr;
     int* gst = nullptr;
@@ -150,6 +151,8 @@ struct nls_handle {
     ~nls_handle() {
         guess_state_free(guess);
         drop_graphs();
+        for (auto e : sev)
+            if (e) (void)hipEventDestroy(e);
         for (auto e : gev)
             if (e) (void)hipEventDestroy(e);
         if (gstream) (void)hipStreamDestroy(gstream);
