@@ -304,10 +304,18 @@ __device__ __forceinline__ void local_residual(const DevMesh& M, const DevMaps& 
 // fixed CSR slots.  Rows with more slots than MS (unstructured meshes of
 // high valence) add into jval in place.
 // ----------------------------------------------------------------------------
-template <bool ELAST>
+//
+// SCALED (the local linear systems): an identity row is multiplied by the
+// power of two above the diagonal entry it would have without its Dirichlet
+// condition, and rb (may be null), the system's right-hand side, with it.  The
+// factorisation then keeps its pivot like its neighbours keep theirs (a 1
+// beside their entries costs an interchange for every Dirichlet dof of the
+// patch); the scaling is exact and the solution the same.
+template <bool ELAST, bool SCALED = false>
 __device__ __forceinline__ void assemble_rows(const DevMesh& M, const DevMaps& P, int n, int rowbase,
                                               int ebase, const double* vp, int a0, int a1,
-                                              double* __restrict__ r, double* __restrict__ jval) {
+                                              double* __restrict__ r, double* __restrict__ jval,
+                                              double* rb = nullptr) {
     constexpr int MS = ELAST ? 18 : 10;
     for (int a = a0 + threadIdx.x; a < a1; a += blockDim.x) {
         const int row = rowbase + a;
@@ -340,7 +348,37 @@ __device__ __forceinline__ void assemble_rows(const DevMesh& M, const DevMaps& P
         double res;
         if (M.dflag[g]) {
             res = vp[a] - M.dval[g];
-            if (jval) add(a, 1.0);
+            double one = 1.0;
+            if (SCALED) {
+                double kd = 0.0;
+                for (int k = P.rinc_ptr[row]; k < P.rinc_ptr[row + 1]; ++k) {
+                    const int code = P.rinc[k];
+                    const int e = ebase + (code >> 2), pos = code & 3;
+                    if (ELAST) {
+                        double X[4][2], ue[4][2], kr[4][2];
+                        int nd[4];
+                        nh_coords(M, P.pe_gid[e], X);
+                        nh_local_values(P, e, vp, nd, ue);
+                        nh_stiff_row(M, X, ue, pos, a & 1, kr);
+#pragma unroll
+                        for (int b = 0; b < 4; ++b)
+                            if (b == pos) kd += (a & 1) ? kr[b][1] : kr[b][0];
+                    } else {
+                        const double uu[3] = {vp[P.pe_conn[3 * e]], vp[P.pe_conn[3 * e + 1]],
+                                              vp[P.pe_conn[3 * e + 2]]};
+                        const int ge = P.pe_gid[e];
+                        const double U = uu[0] + uu[1] + uu[2];
+                        const double m = (U * U + uu[0] * uu[0] + uu[1] * uu[1] + uu[2] * uu[2]) * (1.0 / 12.0);
+                        const double* G = M.G6 + 6 * (size_t)ge;
+                        kd += M.kappa[ge] * (1.0 + M.beta * m) * (pos == 0 ? G[0] : (pos == 1 ? G[1] : G[2]));
+                    }
+                }
+                // (not for a value that is not positive, or too large or small
+                // for the scaled entries)
+                if (kd > 0x1p-200 && kd < 0x1p200) one = scalbn(1.0, ilogb(kd) + 1);
+                if (rb) rb[a] *= one;
+            }
+            if (jval) add(a, one);
         } else if (ELAST) {
             const int c = a & 1;
             double f = 0.0;
@@ -398,10 +436,12 @@ __device__ __forceinline__ void assemble_rows(const DevMesh& M, const DevMaps& P
 
 // Jacobian rows [J_ii | B_i] of the whole local problem into the CSR values
 // jval (slots fixed at setup), accumulated in registers row by row.
+// Identity rows are scaled, and rb (the residual, may be null) with them.
 template <bool ELAST>
 __device__ __forceinline__ void local_jacobian(const DevMesh& M, const DevMaps& P, int n, int rowbase,
-                                               int ebase, const double* vp, double* __restrict__ jval) {
-    assemble_rows<ELAST>(M, P, n, rowbase, ebase, vp, 0, n, nullptr, jval);
+                                               int ebase, const double* vp, double* __restrict__ jval,
+                                               double* rb) {
+    assemble_rows<ELAST, true>(M, P, n, rowbase, ebase, vp, 0, n, nullptr, jval, rb);
 }
 
 // ----------------------------------------------------------------------------
@@ -2117,85 +2157,111 @@ __device__ __forceinline__ double sum_rows16(double v) {
 }
 
 // ----------------------------------------------------------------------------
-// Backward substitution U x = b (b in LDS, FP64, in place) with the factors
-// of band_lu, by the whole workgroup in blocks of 16 rows from the last one
-// up: x_1 = U11^{-1} (b_1 - U12 x_2).  Wavefront t mod 4 takes block t (t = 0
-// the last): lane (r, p) = (l mod 16, l / 16) holds the entries of row r in
-// the columns 4 i + p of the block's strip, NC of them, and the whole row r of
-// U11, scaled by the reciprocal diagonal.  A block's entries are loaded AHEAD
-// rounds of four blocks ahead (two where the registers hold them); the products with all but the next block's
-// unknowns are summed one block ahead; so between two blocks lie four of the
-// products, a sum over four lanes, and U11's 16 steps of a broadcast and an
-// FMA each (1,215 rows, kl = ku = 36: 0.03 ms; 0.2 ms step by step from
-// staged columns, which waited for memory).  All threads call it; b is
+// One substitution (b in LDS, FP64, in place) with the factors of band_lu, by
+// the whole workgroup in blocks of 16 rows: BACK: U x = b from the last block
+// up, x_1 = U11^{-1} (b_1 - U12 x_2); else L x = b, for a factorisation without
+// interchanges, from the first block down, x_1 = L11^{-1} (b_1 - L10 x_0).
+// Wavefront t mod 4 takes the t-th block: lane (r, p) = (l mod 16, l / 16) holds
+// the entries of row r in every fourth column of the block's strip, NC of
+// them, and the whole row r of the diagonal block (scaled by the reciprocal
+// diagonal).  A block's entries are loaded AHEAD rounds of four blocks ahead
+// (two where the registers hold them); the products with all but the previous
+// block's unknowns are summed one block ahead; so between two blocks lie four
+// of the products, a sum over four lanes, and the diagonal block's 15 steps of
+// a broadcast and an FMA each.  Bound by the issue of a block's loads beside
+// that chain (1,215 rows, kl = ku = 36, backward: 0.08 ms; 0.2 ms step by step
+// from staged columns, which waited for memory).  All threads call it; b is
 // complete for every thread on return.
 // ----------------------------------------------------------------------------
-template <typename T, int NC, int AHEAD>
-__device__ __forceinline__ void band_back_blocked(int n_, int kw_, const T* Uf, double* b) {
-    const int n = uniform(n_), kw = uniform(kw_), ldu = kw + 1;
+template <typename T, int NC, int AHEAD, bool BACK>
+__device__ __forceinline__ void band_sweep(int n_, int width_, int ldf_, const T* F, double* b) {
+    // width: entries of a factor column beyond the diagonal (BACK: above it,
+    // kl + ku; else kl); ldf: the column stride
+    const int n = uniform(n_), width = uniform(width_), ldf = uniform(ldf_);
     const int lane = threadIdx.x & 63, wv = uniform((int)(threadIdx.x >> 6));
     const int r = lane & 15, p = lane >> 4, nb = (n + 15) >> 4;
-    const __amdgpu_buffer_rsrc_t Ur = store_range(const_cast<T*>(Uf), (unsigned)(n * ldu) * sizeof(T));
+    const __amdgpu_buffer_rsrc_t Fr = store_range(const_cast<T*>(F), (unsigned)(n * ldf) * sizeof(T));
     struct Block {
-        T u[NC - 4];  // columns 16 + 4 i + p of the strip
-        T u11[16];    // the row of U11
-        T d;          // its diagonal entry
+        T f[NC];    // the strip
+        T f11[16];  // the row of the diagonal block
+        T d;        // its diagonal entry (BACK)
     };
     Block A, B;
-    double far_sum = 0.0;
+    // column i of the lane, relative to the block's first
+    auto column = [&](int i) { return BACK ? 16 + 4 * i + p : p - 4 * (i + 1); };
+    auto first = [&](int t) { return BACK ? 16 * (nb - 1 - t) : 16 * t; };
+    // entry (r, c) of the block at k0: outside the band, before column 0 and
+    // past column n the offset lies outside the factor and gives 0
+    auto entry = [&](int k0, int c) {
+        const unsigned o = BACK ? c - r : r - c - 1;
+        const bool in = BACK ? o <= (unsigned)width : o < (unsigned)width;
+        return range_load(Fr, in ? (unsigned)((k0 + c) * ldf + (int)o) * (unsigned)sizeof(T) : kNoStore, T());
+    };
     auto load = [&](Block& S, int t) {
-        const int k0 = 16 * (nb - 1 - t);
-        if (k0 < 0) return;
+        if (t >= nb) return;
+        const int k0 = first(t);
 #pragma unroll
-        for (int i = 4; i < NC; ++i) {
-            const unsigned c = 4 * i + p, o = c - r;
-            S.u[i - 4] = range_load(
-                Ur, o <= (unsigned)kw ? ((k0 + c) * ldu + o) * (unsigned)sizeof(T) : kNoStore, T());
-        }
+        for (int i = 0; i < NC; ++i) S.f[i] = entry(k0, column(i));
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            const unsigned o = c - r;
-            S.u11[c] = range_load(
-                Ur, o <= (unsigned)kw ? ((k0 + c) * ldu + o) * (unsigned)sizeof(T) : kNoStore, T());
-        }
-        S.d = range_load(Ur, (k0 + r) * ldu * (unsigned)sizeof(T), T());
+        for (int c = 0; c < 16; ++c) S.f11[c] = entry(k0, c);
+        S.d = T(1);
+        if (BACK) S.d = entry(k0, r);
     };
     auto products = [&](const Block& S, int k0, int i0, int i1) {
         double acc = 0.0;
 #pragma unroll
-        for (int i = 4; i < NC; ++i)
-            if (i >= i0 && i < i1) acc += (double)S.u[i - 4] * b[min(k0 + 4 * i + p, n - 1)];
+        for (int i = 0; i < NC; ++i)
+            if (i >= i0 && i < i1)
+                acc += (double)S.f[i] * b[BACK ? min(k0 + column(i), n - 1) : max(k0 + column(i), 0)];
         return acc;
     };
+    // what a block needs beyond the unknowns of the one before it
+    double far_sum = 0.0, rd = 0.0, w[16];
     auto far_part = [&](const Block& S, int t) {
-        if (t < nb) far_sum = products(S, 16 * (nb - 1 - t), 8, NC);
-    };
-    auto near_part = [&](Block& S, int t) {
         if (t >= nb) return;
-        const int k0 = 16 * (nb - 1 - t);
+        const int k0 = first(t);
+        far_sum = products(S, k0, 4, NC);
+        // (rows past n are zeros: their slots of the factor may hold anything)
         const bool in = k0 + r < n;
-        const double rd = in ? 1.0 / (double)S.d : 0.0;
-        double w[16];
+        rd = in ? (BACK ? 1.0 / (double)S.d : 1.0) : 0.0;
 #pragma unroll
-        for (int c = 1; c < 16; ++c) w[c] = c > r ? (double)S.u11[c] * rd : 0.0;
+        for (int c = 0; c < 16; ++c) w[c] = in && (BACK ? c > r : c < r) ? (double)S.f11[c] * rd : 0.0;
+    };
+    auto near_part = [&](const Block& S, int t) {
+        if (t >= nb) return;
+        const int k0 = first(t);
+        const bool in = k0 + r < n;
         double z = b[in ? k0 + r : k0];
-        z = (z - sum_rows16(far_sum + products(S, k0, 4, 8))) * rd;
+        z = (z - sum_rows16(far_sum + products(S, k0, 0, 4))) * rd;
+        z = in ? z : 0.0;
 #pragma unroll
-        for (int c = 15; c > 0; --c) z -= w[c] * rdlane(z, c);
+        for (int i = 0; i < 15; ++i) {
+            const int c = BACK ? 15 - i : i;
+            z -= w[c] * rdlane(z, c);
+        }
         if (lane < 16 && in) b[k0 + r] = z;
-        load(S, t + 4 * AHEAD);
     };
     load(A, wv);
     if (AHEAD == 2) load(B, wv + 4);
-    auto round = [&](Block& S, Block& next, int t0) {
+    if (wv == 0) far_part(A, 0);
+    // block t0 + q: its own wavefront ends it, the next one prepares, and the
+    // one before loads anew
+    auto round = [&](Block& S, Block& other, int t0) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (wv == q)
+            if (wv == q) {
                 near_part(S, t0 + q);
-            else if (wv == q + 1)
-                far_part(S, t0 + q + 1);
-            else if (q == 3 && wv == 0)
-                far_part(next, t0 + 4);
+            } else if (wv == ((q + 1) & 3)) {
+                if (q < 3)
+                    far_part(S, t0 + q + 1);
+                else
+                    far_part(other, t0 + 4);
+            } else if (wv == ((q + 3) & 3)) {
+                if (q > 0)
+                    load(S, t0 + q - 1 + 4 * AHEAD);
+                else if (t0 > 0)
+                    load(other, t0 - 1 + 4 * AHEAD);
+            }
             lds_barrier();
         }
     };
@@ -2213,13 +2279,15 @@ __device__ __forceinline__ void band_back_blocked(int n_, int kw_, const T* Uf, 
 template <typename T>
 __device__ __forceinline__ void band_back(int n, int kw, const T* Uf, double* b) {
     if (kw <= 96)
-        band_back_blocked<T, 28, 2>(n, kw, Uf, b);
+        band_sweep<T, 24, 2, true>(n, kw, kw + 1, Uf, b);
     else
-        band_back_blocked<T, 68, 1>(n, kw, Uf, b);
+        band_sweep<T, 64, 1, true>(n, kw, kw + 1, Uf, b);
 }
 
-// The workgroup's band solve: forward staged when the stage holds 8 or more
-// steps, otherwise by one wavefront, then backward by blocks.  All threads
+// The workgroup's band solve.  Forward: by blocks where the factorisation made
+// no interchange and kl <= 48 (the multipliers then sit in their rows); with
+// interchanges step by step, from staged columns when the stage holds 8 or
+// more steps, otherwise by one wavefront.  Backward by blocks.  All threads
 // call it; b is complete for every thread on return.
 template <typename T, int NPL>
 __device__ __forceinline__ void band_solve_group(int n, int kl, int ku, const T* __restrict__ Uf,
@@ -2227,8 +2295,12 @@ __device__ __forceinline__ void band_solve_group(int n, int kl, int ku, const T*
                                                  double* b, void* stage, int stage_bytes,
                                                  bool backward_only) {
     if (!backward_only) {
+        int moved = kl > 48;
+        for (int k = threadIdx.x; k < n; k += blockDim.x) moved |= piv[k] != k;
         const int G = stage ? band_stage_cols<T, NPL>(stage_bytes) : 0;
-        if (G >= 8) {
+        if (!__syncthreads_or(moved)) {
+            band_sweep<T, 12, 2, false>(n, kl, kl > 1 ? kl : 1, Lf, b);
+        } else if (G >= 8) {
             band_forward_staged<T, NPL>(n, kl, ku, Lf, piv, b, stage, G);
         } else {
             if (threadIdx.x < 64) band_solve_wave<T, NPL, true>(n, kl, ku, Uf, Lf, piv, b);
@@ -2394,7 +2466,7 @@ k_local_newton(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* 
                 if (dprev <= np.stagnation * xm) break;
             }
             if (its == np.maxit) { status = 1; break; }
-            local_jacobian<ELAST>(M, P, n, rowbase, ebase, vp, L.jval);
+            local_jacobian<ELAST>(M, P, n, rowbase, ebase, vp, L.jval, rb);
             // (each thread saves and restores entries of its own)
             for (int a = threadIdx.x; a < n; a += blockDim.x) L.xstar[rowbase + a] = vp[a];
             for (int j = threadIdx.x; j < ng; j += blockDim.x) L.ghost[gbase + j] = vp[n + j];
@@ -2439,7 +2511,7 @@ k_local_newton(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* 
     for (int j = threadIdx.x; j < ng; j += blockDim.x) L.ghost[gbase + j] = vp[n + j];
     if (status == 0 && np.keep_factor) {
         // J and its LU at x*, in FP64, are kept for the exact tangent
-        local_jacobian<ELAST>(M, P, n, rowbase, ebase, vp, L.jval);
+        local_jacobian<ELAST>(M, P, n, rowbase, ebase, vp, L.jval, nullptr);
         __syncthreads();
         if (local_factor<false>(P, L, np, i, n, rowbase, W, wbytes, mult, sflag)) status = 3;
     }
@@ -3307,7 +3379,11 @@ k_tangent_local(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double*
         const int row = rowbase + a;
         double acc = 0.0;
         if (restrict_rhs) {
-            acc = v[P.l2g[row]];  // R_i v (local Schwarz solve)
+            const int g = P.l2g[row];
+            acc = v[g];  // R_i v (local Schwarz solve)
+            if (M.dflag[g])  // the factored identity rows are scaled
+                for (int s = P.jptr[row]; s < P.jptr[row + 1]; ++s)
+                    if (P.jcol[s] == a) acc *= L.jval[s];
         } else {
             for (int s = P.jptr[row]; s < P.jptr[row + 1]; ++s) {
                 const int c = P.jcol[s];
@@ -3446,7 +3522,7 @@ k_local_factor(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* 
     for (int j = threadIdx.x; j < ng; j += blockDim.x)
         vp[n + j] = gloc ? gloc[gbase + j] : u[P.g2g[gbase + j]];
     __syncthreads();
-    local_jacobian<ELAST>(M, P, n, rowbase, ebase, vp, L.jval);
+    local_jacobian<ELAST>(M, P, n, rowbase, ebase, vp, L.jval, nullptr);
     __syncthreads();
     const int wbytes = lds_bytes - (int)((char*)W - (char*)smem);
     const int status = local_factor<false>(P, L, np, i, n, rowbase, W, wbytes, mult, sflag) ? 3 : 0;
@@ -4235,26 +4311,6 @@ __global__ void k_maxpy(const double* __restrict__ V, int64_t ld, int m, const d
     w[t] -= sign * acc;
 }
 
-// w -= sum_j h[j] V[j] and the partial sums of ||w||^2 over the same block
-// chunks as k_mdot_partial (so k_mdot_final with m = 1 completes the norm).
-__global__ void __launch_bounds__(NLS_BLOCK)
-k_maxpy_norm(const double* __restrict__ V, int64_t ld, int m, const double* __restrict__ h,
-             double* __restrict__ w, int n, double* __restrict__ partial) {
-    __shared__ double red[24];
-    const int chunk = (n + gridDim.x - 1) / gridDim.x;
-    const int lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
-    double ss = 0.0;
-    for (int t = lo + threadIdx.x; t < hi; t += blockDim.x) {
-        double acc = 0.0;
-        for (int j = 0; j < m; ++j) acc += h[j] * V[(int64_t)j * ld + t];
-        const double x = w[t] - acc;
-        w[t] = x;
-        ss += x * x;
-    }
-    ss = block_sum(ss, red);
-    if (threadIdx.x == 0) partial[blockIdx.x] = ss;
-}
-
 // ---------------------------------------------------------------------------
 // Arnoldi step kernels that finish the previous reduction themselves: every
 // block adds up the partial sums of the dot products in the same fixed order
@@ -4790,13 +4846,6 @@ hipError_t launch_arnoldi_gs(const double* V, int64_t ld, int m, double* w, int 
     k_maxpy_mdot_totals<<<nb, NLS_BLOCK, lds, s>>>(V, ld, m, partial, nb, h1, w, n, partial2);
     k_maxpy_norm_totals<<<nb, NLS_BLOCK, lds, s>>>(V, ld, m, partial2, nb, h2, w, n, pnorm);
     k_scale_givens_totals<<<nblocks(n), NLS_BLOCK, 0, s>>>(w, vnext, n, pnorm, nb, G, j);
-    return hipGetLastError();
-}
-
-hipError_t launch_maxpy_norm(const double* V, int64_t ld, int m, const double* h, double* w, int n,
-                             double* partial, double* out, int nb, hipStream_t s) {
-    k_maxpy_norm<<<nb, NLS_BLOCK, 0, s>>>(V, ld, m, h, w, n, partial);
-    k_mdot_final<<<1, 256, 0, s>>>(partial, nb, 1, out);
     return hipGetLastError();
 }
 
