@@ -247,6 +247,49 @@ __device__ __forceinline__ void nh_local_values(const DevMaps& P, int e, const d
     }
 }
 
+// The P1 elements of one row, P1_CH at a time: the loads of a chunk go out
+// level by level (incidence codes, then vertices and element, then the row of
+// G and kappa), so that a row waits for four loads in turn and not for three
+// per element (6: the elements around an interior vertex of a regular mesh).
+// f(vertices, vertex values, row of G, kappa) is called for element after
+// element in the order of the incidence list.  512x512, 16x16 subdomains, with
+// Jacobians: 64.5 -> 47.6 us; still bound by the latency of these loads.
+constexpr int P1_CH = 6;
+template <class F>
+__device__ __forceinline__ void p1_row_elements(const DevMesh& M, const DevMaps& P, int row, int ebase,
+                                                const double* vp, F f) {
+    const int ks = P.rinc_ptr[row], ke = P.rinc_ptr[row + 1];
+    for (int k = ks; k < ke; k += P1_CH) {
+        int code[P1_CH], nd[P1_CH][3], ge[P1_CH];
+        double g[P1_CH][3], kap[P1_CH];
+#pragma unroll
+        for (int u = 0; u < P1_CH; ++u) code[u] = P.rinc[min(k + u, ke - 1)];
+#pragma unroll
+        for (int u = 0; u < P1_CH; ++u) {
+            const int e = ebase + (code[u] >> 2);
+            ge[u] = P.pe_gid[e];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) nd[u][c] = P.pe_conn[3 * e + c];
+        }
+#pragma unroll
+        for (int u = 0; u < P1_CH; ++u) {
+            // row pos of the element matrix (stored G00 G11 G22 G01 G12 G20)
+            const int pos = code[u] & 3;
+            const double* G = M.G6 + 6 * (size_t)ge[u];
+            g[u][0] = G[pos == 0 ? 0 : (pos == 1 ? 3 : 5)];
+            g[u][1] = G[pos == 0 ? 3 : (pos == 1 ? 1 : 4)];
+            g[u][2] = G[pos == 0 ? 5 : (pos == 1 ? 4 : 2)];
+            kap[u] = M.kappa[ge[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < P1_CH; ++u)
+            if (k + u < ke) {
+                const double uu[3] = {vp[nd[u][0]], vp[nd[u][1]], vp[nd[u][2]]};
+                f(nd[u], uu, g[u], kap[u]);
+            }
+    }
+}
+
 // detf (LDS word, or null): set to 1 when an elasticity row meets det F <= 0.
 template <bool ELAST>
 __device__ __forceinline__ void local_residual(const DevMesh& M, const DevMaps& P, int n, int rowbase,
@@ -278,19 +321,13 @@ __device__ __forceinline__ void local_residual(const DevMesh& M, const DevMaps& 
             continue;
         }
         double acc = 0.0;
-        for (int k = P.rinc_ptr[row]; k < P.rinc_ptr[row + 1]; ++k) {
-            const int code = P.rinc[k];
-            const int e = ebase + (code >> 2), pos = code & 3;
-            const double u0 = vp[P.pe_conn[3 * e]], u1 = vp[P.pe_conn[3 * e + 1]],
-                         u2 = vp[P.pe_conn[3 * e + 2]];
-            const int ge = P.pe_gid[e];
-            const double U = u0 + u1 + u2;
-            const double m = (U * U + u0 * u0 + u1 * u1 + u2 * u2) * (1.0 / 12.0);
-            double g0, g1, g2;
-            g_row(M.G6 + 6 * (size_t)ge, pos, g0, g1, g2);
-            const double s = g0 * u0 + g1 * u1 + g2 * u2;
-            acc += M.kappa[ge] * (1.0 + M.beta * m) * s;
-        }
+        p1_row_elements(M, P, row, ebase, vp,
+                        [&](const int (&nd)[3], const double (&uu)[3], const double (&g)[3], double kap) {
+            const double U = uu[0] + uu[1] + uu[2];
+            const double m = (U * U + uu[0] * uu[0] + uu[1] * uu[1] + uu[2] * uu[2]) * (1.0 / 12.0);
+            const double sg = g[0] * uu[0] + g[1] * uu[1] + g[2] * uu[2];
+            acc += kap * (1.0 + M.beta * m) * sg;
+        });
         rb[a] = acc - M.bload[g];
     }
 }
@@ -403,18 +440,11 @@ __device__ __forceinline__ void assemble_rows(const DevMesh& M, const DevMaps& P
             res = ok ? f - M.bload[g] : __builtin_nan("");
         } else {
             double f = 0.0;
-            for (int k = P.rinc_ptr[row]; k < P.rinc_ptr[row + 1]; ++k) {
-                const int code = P.rinc[k];
-                const int e = ebase + (code >> 2), pos = code & 3;
-                const int nd[3] = {P.pe_conn[3 * e], P.pe_conn[3 * e + 1], P.pe_conn[3 * e + 2]};
-                const double uu[3] = {vp[nd[0]], vp[nd[1]], vp[nd[2]]};
-                const int ge = P.pe_gid[e];
+            p1_row_elements(M, P, row, ebase, vp,
+                            [&](const int (&nd)[3], const double (&uu)[3], const double (&gr)[3], double kap) {
                 const double U = uu[0] + uu[1] + uu[2];
                 const double m = (U * U + uu[0] * uu[0] + uu[1] * uu[1] + uu[2] * uu[2]) * (1.0 / 12.0);
-                double gr[3];
-                g_row(M.G6 + 6 * (size_t)ge, pos, gr[0], gr[1], gr[2]);
                 const double sg = gr[0] * uu[0] + gr[1] * uu[1] + gr[2] * uu[2];
-                const double kap = M.kappa[ge];
                 const double coef = kap * (1.0 + M.beta * m);
                 f += coef * sg;
                 if (jval) {
@@ -422,7 +452,7 @@ __device__ __forceinline__ void assemble_rows(const DevMesh& M, const DevMaps& P
 #pragma unroll
                     for (int cc = 0; cc < 3; ++cc) add(nd[cc], coef * gr[cc] + rk * (U + uu[cc]));
                 }
-            }
+            });
             res = f - M.bload[g];
         }
         if (r) r[a] = res;
@@ -1421,8 +1451,8 @@ __device__ __forceinline__ int band_lu_gauss(int n_, int kl_, int ku_, const int
 // which stays in L2), but their first 16 columns, which only the panel reads,
 // in LDS.  Wavefront 0 runs the panels; wavefront 1 forms and stores U12 and
 // the panel's columns, wavefronts 2-7 the rows below, 2-5 the entering rows.
-// 434 rows, kl = 87: 0.3 ms with the solve (2.65 ms by band_lu, a barrier per
-// column).
+// 434 rows, kl = 87: 0.47 ms, 0.52 ms with the backward substitution's launch
+// (2.65 ms by band_lu, a barrier per column).
 // ----------------------------------------------------------------------------
 constexpr int WIDE_THREADS = 512;
 __device__ __forceinline__ int band_lu_wide(int n_, int kl_, int ku_, const int* __restrict__ rptr_,
