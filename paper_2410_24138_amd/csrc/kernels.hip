@@ -248,28 +248,31 @@ __device__ __forceinline__ void nh_local_values(const DevMaps& P, int e, const d
 }
 
 // The P1 elements of one row, P1_CH at a time: the loads of a chunk go out
-// level by level (incidence codes, then vertices and element, then the row of
-// G and kappa), so that a row waits for four loads in turn and not for three
-// per element (6: the elements around an interior vertex of a regular mesh).
+// level by level (incidence codes, then vertices and element, then the values
+// there, the row of G and kappa), so that a row waits for four loads in turn
+// and not for three per element (6: the elements around an interior vertex of
+// a regular mesh).
 // f(vertices, vertex values, row of G, kappa) is called for element after
-// element in the order of the incidence list.  512x512, 16x16 subdomains, with
-// Jacobians: 64.5 -> 47.6 us; still bound by the latency of these loads.
+// element in the order of the incidence list inc[ks .. ke) (4 * element +
+// corner; conn and gid: the elements' vertices in vp and their numbers in the
+// mesh, null where the lists are the mesh's own).  512x512, 16x16 subdomains,
+// with Jacobians: 64.5 -> 47.9 us; still bound by the latency of these loads.
 constexpr int P1_CH = 6;
 template <class F>
-__device__ __forceinline__ void p1_row_elements(const DevMesh& M, const DevMaps& P, int row, int ebase,
-                                                const double* vp, F f) {
-    const int ks = P.rinc_ptr[row], ke = P.rinc_ptr[row + 1];
+__device__ __forceinline__ void p1_elements(const DevMesh& M, const int* __restrict__ inc, int ks, int ke,
+                                            const int* __restrict__ conn, const int* __restrict__ gid,
+                                            const double* vp, F f) {
     for (int k = ks; k < ke; k += P1_CH) {
         int code[P1_CH], nd[P1_CH][3], ge[P1_CH];
-        double g[P1_CH][3], kap[P1_CH];
+        double g[P1_CH][3], kap[P1_CH], uu[P1_CH][3];
 #pragma unroll
-        for (int u = 0; u < P1_CH; ++u) code[u] = P.rinc[min(k + u, ke - 1)];
+        for (int u = 0; u < P1_CH; ++u) code[u] = inc[min(k + u, ke - 1)];
 #pragma unroll
         for (int u = 0; u < P1_CH; ++u) {
-            const int e = ebase + (code[u] >> 2);
-            ge[u] = P.pe_gid[e];
+            const int e = code[u] >> 2;
+            ge[u] = gid ? gid[e] : e;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) nd[u][c] = P.pe_conn[3 * e + c];
+            for (int c = 0; c < 3; ++c) nd[u][c] = conn[3 * e + c];
         }
 #pragma unroll
         for (int u = 0; u < P1_CH; ++u) {
@@ -280,14 +283,21 @@ __device__ __forceinline__ void p1_row_elements(const DevMesh& M, const DevMaps&
             g[u][1] = G[pos == 0 ? 3 : (pos == 1 ? 1 : 4)];
             g[u][2] = G[pos == 0 ? 5 : (pos == 1 ? 4 : 2)];
             kap[u] = M.kappa[ge[u]];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) uu[u][c] = vp[nd[u][c]];
         }
 #pragma unroll
         for (int u = 0; u < P1_CH; ++u)
-            if (k + u < ke) {
-                const double uu[3] = {vp[nd[u][0]], vp[nd[u][1]], vp[nd[u][2]]};
-                f(nd[u], uu, g[u], kap[u]);
-            }
+            if (k + u < ke) f(nd[u], uu[u], g[u], kap[u]);
     }
+}
+
+// the same over the elements of one row of a patch
+template <class F>
+__device__ __forceinline__ void p1_row_elements(const DevMesh& M, const DevMaps& P, int row, int ebase,
+                                                const double* vp, F f) {
+    p1_elements(M, P.rinc, P.rinc_ptr[row], P.rinc_ptr[row + 1], P.pe_conn + 3 * (size_t)ebase,
+                P.pe_gid + ebase, vp, f);
 }
 
 // detf (LDS word, or null): set to 1 when an elasticity row meets det F <= 0.
@@ -3429,6 +3439,30 @@ k_tangent_local(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double*
     for (int a = threadIdx.x; a < n; a += blockDim.x) L.z[rowbase + a] = rb[a];
 }
 
+// row ph (nk entries) of Phi times the coarse vector c: eight entries' indices
+// and values are loaded before any is added
+__device__ __forceinline__ double phi_row(const double* __restrict__ ph, const int* __restrict__ kl, int nk,
+                                          const double* __restrict__ c) {
+    constexpr int CH = 8;
+    double acc = 0.0;
+    for (int l0 = 0; l0 < nk; l0 += CH) {
+        int ix[CH];
+        double p[CH], v[CH];
+#pragma unroll
+        for (int q = 0; q < CH; ++q) {
+            const int l = min(l0 + q, nk - 1);
+            ix[q] = kl[l];
+            p[q] = ph[l];
+        }
+#pragma unroll
+        for (int q = 0; q < CH; ++q) v[q] = c[ix[q]];
+#pragma unroll
+        for (int q = 0; q < CH; ++q)
+            if (l0 + q < nk) acc += p[q] * v[q];
+    }
+    return acc;
+}
+
 // out[g] = T[own(g)] (+ addv[g]) (+ sum_l Phi_o(g)[g][l] c[K_o(g)[l]]):
 // restricted prolongation (eq. 8) and the coarse term P_0 c (eq. 10).
 __global__ void k_prolong(int N, const int* __restrict__ own_pidx, const double* __restrict__ T,
@@ -3442,9 +3476,7 @@ __global__ void k_prolong(int N, const int* __restrict__ own_pidx, const double*
         const int o = C.cown[g];
         const int k0 = C.off_k[o], nk = C.off_k[o + 1] - k0;
         const double* ph = C.phi + C.off_phi[o] + (int64_t)(C.cpos[g] - C.off_c[o]) * nk;
-        double acc = 0.0;
-        for (int l = 0; l < nk; ++l) acc += ph[l] * cvec[C.klist[k0 + l]];
-        y += acc;
+        y += phi_row(ph, C.klist + k0, nk, cvec);
     }
     out[g] = y;
 }
@@ -3571,12 +3603,12 @@ __global__ void k_sub_coarse(int N, DevCoarse C, const double* __restrict__ cvec
     const int o = C.cown[g];
     const int k0 = C.off_k[o], nk = C.off_k[o + 1] - k0;
     const double* ph = C.phi + C.off_phi[o] + (int64_t)(C.cpos[g] - C.off_c[o]) * nk;
-    double acc = 0.0;
-    for (int l = 0; l < nk; ++l) acc += ph[l] * cvec[C.klist[k0 + l]];
-    out[g] = v[g] - acc;
+    out[g] = v[g] - phi_row(ph, C.klist + k0, nk, cvec);
 }
 
-// Global residual F(u) (eq. 3): node-centric over incident elements.
+// Global residual F(u) (eq. 3): node-centric over incident elements.  On a small
+// mesh it is one wave's latency, so a workgroup is one wave, on a CU of its own
+// (64x64, the call: 18.0 -> 16.2 us).
 __global__ void k_global_residual(DevMesh M, const double* __restrict__ u, double* __restrict__ F) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= M.N) return;
@@ -3585,16 +3617,12 @@ __global__ void k_global_residual(DevMesh M, const double* __restrict__ u, doubl
         return;
     }
     double acc = 0.0;
-    for (int k = M.nptr[g]; k < M.nptr[g + 1]; ++k) {
-        const int code = M.nel[k];
-        const int e = code >> 2, pos = code & 3;
-        const double u0 = u[M.conn[3 * e]], u1 = u[M.conn[3 * e + 1]], u2 = u[M.conn[3 * e + 2]];
-        const double U = u0 + u1 + u2;
-        const double m = (U * U + u0 * u0 + u1 * u1 + u2 * u2) * (1.0 / 12.0);
-        double g0, g1, g2;
-        g_row(M.G6 + 6 * (size_t)e, pos, g0, g1, g2);
-        acc += M.kappa[e] * (1.0 + M.beta * m) * (g0 * u0 + g1 * u1 + g2 * u2);
-    }
+    p1_elements(M, M.nel, M.nptr[g], M.nptr[g + 1], M.conn, nullptr, u,
+                [&](const int (&nd)[3], const double (&uu)[3], const double (&gr)[3], double kap) {
+        const double U = uu[0] + uu[1] + uu[2];
+        const double m = (U * U + uu[0] * uu[0] + uu[1] * uu[1] + uu[2] * uu[2]) * (1.0 / 12.0);
+        acc += kap * (1.0 + M.beta * m) * (gr[0] * uu[0] + gr[1] * uu[1] + gr[2] * uu[2]);
+    });
     F[g] = acc - M.bload[g];
 }
 
@@ -4560,7 +4588,7 @@ hipError_t launch_global_residual(const DevMesh& M, const double* u, double* F, 
     if (M.kind == NLS_PROBLEM_NEOHOOKE)
         k_global_residual_nh<<<nblocks(M.ndof), NLS_BLOCK, 0, s>>>(M, u, F);
     else
-        k_global_residual<<<nblocks(M.N), NLS_BLOCK, 0, s>>>(M, u, F);
+        k_global_residual<<<(M.N + 63) / 64, 64, 0, s>>>(M, u, F);
     return hipGetLastError();
 }
 
