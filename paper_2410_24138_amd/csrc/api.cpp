@@ -980,7 +980,7 @@ static int coarse_solve(nls_handle* h, const double* u, int* its_out, hipStream_
             h->coarse_inv_valid = false;
         } else if (h->coarse_inv_valid) {
             // chord step with the explicit inverse of the same factorisation
-            HIPCHK(launch_coarse_apply_inverse(d, d.rhs, h->rhs2, cs));
+            HIPCHK(launch_coarse_apply_inverse(d, d.rhs, h->rhs2, 0, cs));
             HIPCHK(hipMemcpyAsync(d.rhs, h->rhs2, sizeof(double) * n0, hipMemcpyDeviceToDevice, cs));
         } else {
             HIPCHK(launch_coarse_lu(d, 0, h->lds_coarse_lu, h->npl_coarse, cs));
@@ -1317,7 +1317,7 @@ static int autotune_coarse(nls_handle* h) {
         return NLS_OK;
     }, &t_inv));
     RC(time_ms(h, [&]() -> int {
-        HIPCHK(launch_coarse_apply_inverse(d, d.rhs, h->rhs2, h->stream));
+        HIPCHK(launch_coarse_apply_inverse(d, d.rhs, h->rhs2, 0, h->stream));
         return NLS_OK;
     }, &t_apply));
     RC(time_ms(h, [&]() -> int {
@@ -1358,11 +1358,10 @@ static int tangent(nls_handle* h, const double* v, double* y, hipStream_t s = nu
         HIPCHK(launch_coarse_ty(d, v, h->lds_coarse_q, s));
         HIPCHK(launch_coarse_gather(d, s));
         if (h->coarse_inv) {
-            HIPCHK(launch_coarse_apply_inverse(d, d.rhs, h->rhs2, s));
-            HIPCHK(launch_coarse_scatter(d, h->rhs2, h->ctmp, s));
+            HIPCHK(launch_coarse_apply_inverse(d, d.rhs, h->ctmp, 1, s));
         } else {
             HIPCHK(launch_coarse_lu(d, 0, h->lds_coarse_lu, h->npl_coarse, s));
-            HIPCHK(launch_coarse_scatter(d, nullptr, h->ctmp, s));
+            HIPCHK(launch_coarse_scatter(d, h->ctmp, s));
         }
         return NLS_OK;
     };
@@ -1803,11 +1802,10 @@ static int nks_precond(nls_handle* h, const double* x, hipStream_t s) {
         HIPCHK(launch_coarse_phit(d, x, s));
         HIPCHK(launch_coarse_gather(d, s));
         if (h->coarse_inv) {
-            HIPCHK(launch_coarse_apply_inverse(d, d.rhs, h->rhs2, s));
-            HIPCHK(launch_coarse_scatter(d, h->rhs2, h->ctmp, s));
+            HIPCHK(launch_coarse_apply_inverse(d, d.rhs, h->ctmp, 1, s));
         } else {
             HIPCHK(launch_coarse_lu(d, 0, h->lds_coarse_lu, h->npl_coarse, s));
-            HIPCHK(launch_coarse_scatter(d, nullptr, h->ctmp, s));
+            HIPCHK(launch_coarse_scatter(d, h->ctmp, s));
         }
         HIPCHK(launch_prolong(h->dm, h->dp, h->dl.z, &d, h->ctmp, h->zbuf, nullptr, s));
     } else {

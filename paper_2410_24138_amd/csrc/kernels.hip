@@ -3386,18 +3386,22 @@ __global__ void __launch_bounds__(INV_THREADS) k_coarse_inverse(DevCoarse C, int
     }
 }
 
-// y = A0^{-1} x, block by block: one wavefront per row.
+// y = A0^{-1} x, block by block: one wavefront per entry of y, in band order or
+// (ids) by coarse ids, which saves the launch of a permutation (a tangent
+// product of 512x512, 16x16 subdomains: 89.4 -> 86.9 us).
 __global__ void __launch_bounds__(256)
-k_coarse_apply_inverse(DevCoarse C, const double* __restrict__ x, double* __restrict__ y) {
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= C.n0) return;
+k_coarse_apply_inverse(DevCoarse C, const double* __restrict__ x, double* __restrict__ y, int ids) {
+    const int k = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (k >= C.n0) return;
+    const int row = ids ? C.perm[k] : k;
     const int b = C.rblk[row];
     const int off = C.boff[b], n = C.boff[b + 1] - off;
     const double* a = C.a0inv + C.offI[b] + (size_t)(row - off) * n;
     double acc = 0.0;
+#pragma unroll 4
     for (int j = lane; j < n; j += 64) acc += a[j] * x[off + j];
     acc = wave_sum(acc);
-    if (lane == 0) y[row] = acc;
+    if (lane == 0) y[k] = acc;
 }
 
 
@@ -4316,9 +4320,9 @@ __global__ void __launch_bounds__(NLS_BLOCK) k_coarse_update(DevCoarse C) {
 }
 
 // cout[k] = rhs[perm[k]] (band order back to coarse ids).
-__global__ void k_coarse_scatter(DevCoarse C, const double* __restrict__ src, double* __restrict__ cout) {
+__global__ void k_coarse_scatter(DevCoarse C, double* __restrict__ cout) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < C.n0) cout[k] = src[C.perm[k]];
+    if (k < C.n0) cout[k] = C.rhs[C.perm[k]];
 }
 
 // ----------------------------------------------------------------------------
@@ -4795,8 +4799,8 @@ hipError_t launch_coarse_update(const DevCoarse& C, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_coarse_scatter(const DevCoarse& C, const double* src, double* cout, hipStream_t s) {
-    k_coarse_scatter<<<nblocks(C.n0), NLS_BLOCK, 0, s>>>(C, src ? src : C.rhs, cout);
+hipError_t launch_coarse_scatter(const DevCoarse& C, double* cout, hipStream_t s) {
+    k_coarse_scatter<<<nblocks(C.n0), NLS_BLOCK, 0, s>>>(C, cout);
     return hipGetLastError();
 }
 
@@ -4878,8 +4882,9 @@ hipError_t launch_coarse_inverse(const DevCoarse& C, int max_block, int max_ldu,
 }
 
 
-hipError_t launch_coarse_apply_inverse(const DevCoarse& C, const double* x, double* y, hipStream_t s) {
-    k_coarse_apply_inverse<<<(C.n0 + 3) / 4, 256, 0, s>>>(C, x, y);
+hipError_t launch_coarse_apply_inverse(const DevCoarse& C, const double* x, double* y, int ids,
+                                       hipStream_t s) {
+    k_coarse_apply_inverse<<<(C.n0 + 3) / 4, 256, 0, s>>>(C, x, y, ids);
     return hipGetLastError();
 }
 

@@ -208,7 +208,7 @@ hipError_t launch_coarse_gather(const DevCoarse& C, hipStream_t s);
 hipError_t launch_coarse_lu(const DevCoarse& C, int factor, int lds_bytes, int nb_per_lane,
                             hipStream_t s);
 hipError_t launch_coarse_update(const DevCoarse& C, hipStream_t s);
-hipError_t launch_coarse_scatter(const DevCoarse& C, const double* src, double* cout, hipStream_t s);
+hipError_t launch_coarse_scatter(const DevCoarse& C, double* cout, hipStream_t s);
 
 int mrhs_bucket_kl(int kl, int ku);
 int mrhs_lds_bytes(int kl_bucket);
@@ -224,7 +224,8 @@ hipError_t launch_tangent_gemv(const DevMaps& P, const DevTangent& Tg, const dou
 // A0^{-1} per diagonal block from its band LU (any band up to 511 wide)
 int coarse_inverse_lds_bytes(int max_block, int max_ldu);
 hipError_t launch_coarse_inverse(const DevCoarse& C, int max_block, int max_ldu, hipStream_t s);
-hipError_t launch_coarse_apply_inverse(const DevCoarse& C, const double* x, double* y, hipStream_t s);
+hipError_t launch_coarse_apply_inverse(const DevCoarse& C, const double* x, double* y, int ids,
+                                       hipStream_t s);
 
 // vector kernels for GMRES (deterministic reductions)
 hipError_t launch_mdot(const double* V, int64_t ld, int m, const double* w, int n,
