@@ -4014,6 +4014,42 @@ k_coarse_galerkin(DevMesh M, DevCoarse C, const double* __restrict__ w, int with
         // with rows on every closure dof (Dirichlet ones included: Phi is
         // zero there, so they do not change A_i, but Y needs them)
         double* y = C.ybuf + C.off_phi[i];
+        // rows accumulated in registers where the subdomain meets at most
+        // GAL_E coarse functions (a box: 4 vertices of 2 and 4 edges of 3),
+        // else read, added to and written back for every element (set-up of an
+        // outer step of 256x128, 64 unequal subdomains: 10.0 -> 8.6 ms)
+        constexpr int GAL_E = 24;
+        if (nk <= GAL_E) {
+            for (int a = a0 + threadIdx.x; a < a1; a += blockDim.x) {
+                double acc[GAL_E];
+#pragma unroll
+                for (int l = 0; l < GAL_E; ++l) acc[l] = 0.0;
+                for (int t = C.cinc_ptr[cb + a]; t < C.cinc_ptr[cb + a + 1]; ++t) {
+                    const int code = C.cinc[t];
+                    const int e = eb + (code >> 2), pos = code & 3;
+                    double kr[4][2];
+                    int cn[4];
+                    coarse_elem_row<true>(M, C, cb, e, pos, a & 1, w, kr, cn);
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+#pragma unroll
+                        for (int kk = 0; kk < 2; ++kk) {
+                            const double* pr = ph + (int64_t)(2 * cn[b] + kk) * nk;
+#pragma unroll
+                            for (int l = 0; l < GAL_E; ++l)
+                                if (l < nk) acc[l] += kr[b][kk] * pr[l];
+                        }
+                }
+                double* zr = z + (int64_t)a * nk;
+#pragma unroll
+                for (int l = 0; l < GAL_E; ++l)
+                    if (l < nk) {
+                        zr[l] = acc[l];
+                        if (with_y) y[(int64_t)l * nc + a] = acc[l];
+                    }
+            }
+            return;
+        }
         for (int a = a0 + threadIdx.x; a < a1; a += blockDim.x) {
             double* zr = z + (int64_t)a * nk;
             for (int l = 0; l < nk; ++l) zr[l] = 0.0;
