@@ -105,12 +105,12 @@ typedef struct nls_options {
 /* options.flags: time the local-solve and local-tangent kernels with HIP
    events on the handle's stream (adds one event pair per launch). */
 #define NLS_FLAG_PROFILE  1
-/* options.flags: run GMRES with the Hessenberg rotations on the device and
-   every block of 4 Arnoldi steps replayed as one HIP graph (captured on
-   first use on a stream of the library's own), one host synchronisation
-   per block instead of per step.  Used when the tangent has its explicit
-   local blocks and, for two-level coupling, an explicit coarse inverse;
-   otherwise GMRES runs step by step. */
+/* options.flags: run GMRES with every block of 4 Arnoldi steps replayed as
+   one HIP graph (captured on first use on a stream of the library's own),
+   one host synchronisation per block.  Used when the tangent has its
+   explicit local blocks and, for two-level coupling, an explicit coarse
+   inverse; otherwise GMRES runs step by step, the host reading a step's
+   state while the next one runs. */
 #define NLS_FLAG_GRAPH    2
 /* options.flags: the coarse iteration for T_0 (eq. (9)) takes chord steps
    with the last factorisation of A0 (from the previous evaluation or its
