@@ -1410,6 +1410,7 @@ __device__ __forceinline__ int band_lu_gauss(int n_, int kl_, int ku_, const int
             lds_barrier();
             T* const E = Wb + (kl + RPW * (wv - 2)) * ld;
             for (int c = lane; c < RPW * ld; c += 64) E[c] = T(0);
+            wave_sync();  // entries go into words that other lanes cleared
 #pragma unroll
             for (int u = 0; u < PF; ++u)
                 if (ec[u] >= 0 && ec[u] < n) Wb[(kl + eq) * ld + (ec[u] - k1)] = T(ev[u]);
@@ -1803,6 +1804,7 @@ __device__ __forceinline__ int band_lu_wide(int n_, int kl_, int ku_, const int*
                 double* const E = Wb + (kl + RPW * (wv - 2)) * ld;
                 for (int c = lane; c < RPW * ld; c += 64) E[c] = 0.0;
                 for (int c = lane; c < RPW * LC; c += 64) Cb[(kl + RPW * (wv - 2)) * LC + c] = 0.0;
+                wave_sync();  // entries go into words that other lanes cleared
 #pragma unroll
                 for (int u = 0; u < PF; ++u)
                     if (ec[u] >= 0 && ec[u] < n) put(Wb, Cb, kl + eq, ec[u] - k1, ev[u]);
