@@ -1072,6 +1072,16 @@ __device__ __forceinline__ P* uniform(P* p) {
     return (P*)(((unsigned long long)hi << 32) | lo);
 }
 
+// The same value, unknown to the compiler: masks and offsets formed from it are
+// taken anew where they are used.  Those formed from the lane number itself do
+// not change in a loop, are hoisted out of it, and fill the registers (the
+// fused local Newton kernel, diffusion: 676 bytes of scratch per lane, 0 with
+// the strips' and tiles' lane numbers taken anew).
+__device__ __forceinline__ int anew(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // Stores through a buffer resource over [base, base + bytes): an offset past
 // its end is dropped by the hardware's range check, so a store that only some
 // lanes make needs no branch (those lanes take offset kNoStore).
@@ -1199,7 +1209,7 @@ __device__ __forceinline__ int band_lu_gauss(int n_, int kl_, int ku_, const int
         T ga[4], bv[CT][4];
         acc_t acc[CT];
         int sb[4];
-        const int r = 16 * rt + li;
+        const int li = anew(lane & 15), lk = anew(lane >> 4), r = 16 * rt + li;
         const T* w = src + NB + 16 * ct;
         const T* c = w + __umul24(sig[r], ld) + Mfma<T>::row(lk, 0);
 #pragma unroll
@@ -1283,8 +1293,7 @@ __device__ __forceinline__ int band_lu_gauss(int n_, int kl_, int ku_, const int
         for (int k0 = 0; k0 < n; k0 += NB) {
             // the lane number anew in every panel: the comparisons with it
             // are cheaper taken again than kept in spilled scalar registers
-            int ln = lane;
-            asm volatile("" : "+v"(ln));
+            const int ln = anew(lane);
             const bool have = ln < H;
             T* const Pk = Ps + (k0 & NB) * 64;
             T p[NB], g[NB];
@@ -1643,8 +1652,7 @@ __device__ __forceinline__ int band_lu_wide(int n_, int kl_, int ku_, const int*
     if (wv == 0) {
         bool search = false;
         for (int k0 = 0; k0 < n; k0 += NB) {
-            int ln = lane;
-            asm volatile("" : "+v"(ln));
+            const int ln = anew(lane);
             const bool have[2] = {ln < H, ln + 64 < H};
             double* const Pk = Ps + (k0 & NB) * LP;
             double p[2][NB], g[2][NB];
@@ -2221,7 +2229,7 @@ __device__ __forceinline__ void band_sweep(int n_, int width_, int ldf_, const T
     // kl + ku; else kl); ldf: the column stride
     const int n = uniform(n_), width = uniform(width_), ldf = uniform(ldf_);
     const int lane = threadIdx.x & 63, wv = uniform((int)(threadIdx.x >> 6));
-    const int r = lane & 15, p = lane >> 4, nb = (n + 15) >> 4;
+    const int nb = (n + 15) >> 4;
     const __amdgpu_buffer_rsrc_t Fr = store_range(const_cast<T*>(F), (unsigned)(n * ldf) * sizeof(T));
     struct Block {
         T f[NC];    // the strip
@@ -2229,39 +2237,41 @@ __device__ __forceinline__ void band_sweep(int n_, int width_, int ldf_, const T
         T d;        // its diagonal entry (BACK)
     };
     Block A, B;
-    // column i of the lane, relative to the block's first
-    auto column = [&](int i) { return BACK ? 16 + 4 * i + p : p - 4 * (i + 1); };
+    // row of the lane in its block, and its column i relative to the block's first
+    auto row = [&]() { return anew(lane & 15); };
+    auto column = [](int p, int i) { return BACK ? 16 + 4 * i + p : p - 4 * (i + 1); };
     auto first = [&](int t) { return BACK ? 16 * (nb - 1 - t) : 16 * t; };
     // entry (r, c) of the block at k0: outside the band, before column 0 and
     // past column n the offset lies outside the factor and gives 0
-    auto entry = [&](int k0, int c) {
+    auto entry = [&](int k0, int r, int c) {
         const unsigned o = BACK ? c - r : r - c - 1;
         const bool in = BACK ? o <= (unsigned)width : o < (unsigned)width;
         return range_load(Fr, in ? (unsigned)((k0 + c) * ldf + (int)o) * (unsigned)sizeof(T) : kNoStore, T());
     };
     auto load = [&](Block& S, int t) {
         if (t >= nb) return;
-        const int k0 = first(t);
+        const int k0 = first(t), r = row(), p = anew(lane >> 4);
 #pragma unroll
-        for (int i = 0; i < NC; ++i) S.f[i] = entry(k0, column(i));
+        for (int i = 0; i < NC; ++i) S.f[i] = entry(k0, r, column(p, i));
 #pragma unroll
-        for (int c = 0; c < 16; ++c) S.f11[c] = entry(k0, c);
+        for (int c = 0; c < 16; ++c) S.f11[c] = entry(k0, r, c);
         S.d = T(1);
-        if (BACK) S.d = entry(k0, r);
+        if (BACK) S.d = entry(k0, r, r);
     };
     auto products = [&](const Block& S, int k0, int i0, int i1) {
+        const int p = lane >> 4;
         double acc = 0.0;
 #pragma unroll
         for (int i = 0; i < NC; ++i)
             if (i >= i0 && i < i1)
-                acc += (double)S.f[i] * b[BACK ? min(k0 + column(i), n - 1) : max(k0 + column(i), 0)];
+                acc += (double)S.f[i] * b[BACK ? min(k0 + column(p, i), n - 1) : max(k0 + column(p, i), 0)];
         return acc;
     };
     // what a block needs beyond the unknowns of the one before it
     double far_sum = 0.0, rd = 0.0, w[16];
     auto far_part = [&](const Block& S, int t) {
         if (t >= nb) return;
-        const int k0 = first(t);
+        const int k0 = first(t), r = row();
         far_sum = products(S, k0, 4, NC);
         // (rows past n are zeros: their slots of the factor may hold anything)
         const bool in = k0 + r < n;
@@ -2271,7 +2281,7 @@ __device__ __forceinline__ void band_sweep(int n_, int width_, int ldf_, const T
     };
     auto near_part = [&](const Block& S, int t) {
         if (t >= nb) return;
-        const int k0 = first(t);
+        const int k0 = first(t), r = row();
         const bool in = k0 + r < n;
         double z = b[in ? k0 + r : k0];
         z = (z - sum_rows16(far_sum + products(S, k0, 0, 4))) * rd;
