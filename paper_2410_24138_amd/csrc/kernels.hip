@@ -2364,13 +2364,16 @@ __device__ __forceinline__ void band_solve_group(int n, int kl, int ku, const T*
 
 // Solve J d = rb in place (rb in LDS).  FP64 factors: one band solve.  FP32
 // factors: iterative refinement with FP64 residuals r0 - J d computed from
-// the FP64 CSR values (columns < n), until ||res|| <= ir_rtol ||r0||.
+// the FP64 CSR values (columns < n), until ||res|| <= ir_rtol nr0.  nr0: the
+// norm of the right-hand side before its identity rows were scaled (where an
+// iterate misses Dirichlet values, the scaled entries would loosen the bound of
+// the other rows); the identity rows' own residual is zero after one solve.
 // stage (LDS, stage_bytes; may be null): staging space of the band solves.
 template <int NPL, bool MIXED>
 __device__ __forceinline__ void local_linear_solve(const DevMaps& P, const DevLocal& L, const NewtonParams& np,
                                    int i, int n, int rowbase, double* rb, double* r0,
-                                   double* dl, double* red, bool forward_done = false,
-                                   void* stage = nullptr, int stage_bytes = 0) {
+                                   double* dl, double* red, double nr0, bool forward_done,
+                                   void* stage, int stage_bytes) {
     const int kl = P.kl[i], ku = P.ku[i];
     const int* piv = L.piv + rowbase;
     if (!MIXED) {
@@ -2380,13 +2383,10 @@ __device__ __forceinline__ void local_linear_solve(const DevMaps& P, const DevLo
     }
     const float* Us = L.Uf32 + P.off_u[i];
     const float* Ls = L.Lf32 + P.off_l[i];
-    double nr0 = 0.0;
     for (int a = threadIdx.x; a < n; a += blockDim.x) {
         r0[a] = rb[a];
         dl[a] = 0.0;
-        nr0 += rb[a] * rb[a];
     }
-    nr0 = sqrt(block_sum(nr0, red));
     for (int it = 0;; ++it) {
         band_solve_group<float, NPL>(n, kl, ku, Us, Ls, piv, rb, stage, stage_bytes, false);
         double rr = 0.0;
@@ -2537,7 +2537,7 @@ k_local_newton(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double* 
             }
             // the factorisation window is free during the solve: it holds
             // the staged factor columns
-            local_linear_solve<NPL, MIXED>(P, L, np, i, n, rowbase, rb, r0, dl, red, !MIXED, W,
+            local_linear_solve<NPL, MIXED>(P, L, np, i, n, rowbase, rb, r0, dl, red, rn, !MIXED, W,
                                            wbytes);
             restore();
             double dm = 0.0;
@@ -3450,8 +3450,14 @@ k_tangent_local(DevMesh M, DevMaps P, DevLocal L, NewtonParams np, const double*
     }
     __syncthreads();
     double* stage = red + 24;
-    local_linear_solve<NPL, MIXED>(P, L, np, i, n, rowbase, rb, r0, dl, red, false, stage,
-                            lds_bytes - (int)((char*)stage - (char*)smem));
+    // (mixed handles never restrict here: no scaled entry in rb)
+    double nr0 = 0.0;
+    if (MIXED) {
+        for (int a = threadIdx.x; a < n; a += blockDim.x) nr0 += rb[a] * rb[a];
+        nr0 = sqrt(block_sum(nr0, red));
+    }
+    local_linear_solve<NPL, MIXED>(P, L, np, i, n, rowbase, rb, r0, dl, red, nr0, false, stage,
+                                   lds_bytes - (int)((char*)stage - (char*)smem));
     for (int a = threadIdx.x; a < n; a += blockDim.x) L.z[rowbase + a] = rb[a];
 }
 
