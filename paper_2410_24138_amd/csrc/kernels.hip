@@ -420,9 +420,11 @@ __device__ __forceinline__ void assemble_rows(const DevMesh& M, const DevMaps& P
                         kd += M.kappa[ge] * (1.0 + M.beta * m) * (pos == 0 ? G[0] : (pos == 1 ? G[1] : G[2]));
                     }
                 }
-                // (not for a value that is not positive, or too large or small
-                // for the scaled entries)
-                if (kd > 0x1p-200 && kd < 0x1p200) one = scalbn(1.0, ilogb(kd) + 1);
+                // (not for a value that is not positive, or so large or small
+                // that the factors' range, binary32 in mixed handles, could not
+                // hold it: elements whose vertices are all Dirichlet have
+                // coefficients that no other row sees)
+                if (kd > 0x1p-100 && kd < 0x1p100) one = scalbn(1.0, ilogb(kd) + 1);
                 if (rb) rb[a] *= one;
             }
             if (jval) add(a, one);

@@ -45,3 +45,26 @@ def test_refinement_where_the_iterate_misses_dirichlet_values(kappa):
         assert list(s.inner_iterations()) == [1, 1]
         # both stop at a residual of 1e-8 of about sqrt(n); ||J^{-1}|| <= 1
         assert np.abs(F - ref).max() <= 1e-7
+
+
+# Elements whose vertices are all Dirichlet: no other row sees their
+# coefficient, however far it lies outside the range of binary32 (2^129 and
+# 2^-148), so the results are those of coefficient 1 there.  The solves stop at
+# the same Newton step; the rest is rounding, bounded by cond(J_ii) eps ~ 1e3 *
+# 1e-16 per solve: 1e-11 for F_x and 1e-10 for the tangent.
+@pytest.mark.parametrize("precision", ["fp64", "fp32_ir"])
+@pytest.mark.parametrize("kappa", [2.0 ** 129, 2.0 ** -148])
+def test_coefficients_outside_binary32_between_dirichlet_nodes(kappa, precision):
+    case = synth.diffusion_case(12, 8, synth.even_cuts(12, 2), synth.even_cuts(8, 1), 1)
+    fixed = np.zeros(len(case["xy"]), bool)
+    fixed[case["dirichlet"]] = True
+    corner = fixed[case["conn"]].all(axis=1)
+    assert corner.any()
+    case["elem_coef"] = np.where(corner, kappa, 1.0)
+    S = Schwarz(P1Problem(case), "one_level")
+    rng = np.random.default_rng(4)
+    u, v = rng.normal(size=S.P.N), rng.normal(size=S.P.N)
+    s = _solver(case, precision=precision)
+    for got, ref, tol in ((s.precond_residual(u), S.evaluate(u), 1e-11),
+                          (s.tangent(v), S.tangent(v), 1e-10)):
+        assert np.abs(got.cpu().numpy() - ref).max() <= tol * np.abs(ref).max()
