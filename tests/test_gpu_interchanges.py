@@ -1,0 +1,146 @@
+"""Local factorisations that interchange rows, against the oracle.
+
+The identity rows of a patch are scaled and interchange nothing, so the
+interchanges come from the equations: at a rough iterate of unit size with beta =
+100 (and a rough coefficient) the derivative of the coefficient is large beside
+the diagonal, and the Jacobians, with their identity rows scaled as the kernels
+scale them, interchange rows in tens of columns.  Every test counts them with
+the oracle's LU before it runs the GPU.  Four boxes: the last rows of the lower
+ones are no identity rows.
+
+(half, nyh): a box is half x nyh cells, kl = half + 2, so that 46 is the widest
+band of one window row per lane, 50 takes the 8-column panels and the tangent's
+sweeps, and 58 the unblocked factorisation and one solve per tangent product."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import NKS, P1Problem, Schwarz
+from oracle.schwarz import band_lu_factor
+from tests._lib import ensure_built
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -52
+# (half, nyh, seed)
+SIZES = [(3, 6, 2), (13, 20, 0), (30, 18, 1), (46, 7, 0), (50, 6, 0), (58, 5, 4)]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    ensure_built()
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _case(half, nyh, seed, rough):
+    nx, ny = 2 * half, 2 * nyh
+    case = synth.diffusion_case(nx, ny, synth.even_cuts(nx, 2), synth.even_cuts(ny, 2), 1, beta=100.0)
+    rng = np.random.default_rng(seed)
+    if rough:
+        case["elem_coef"] = np.exp(rng.normal(size=len(case["conn"])))
+    return case, rng.normal(size=len(case["xy"])), rng
+
+
+def _scaled(S, i, x, tr):
+    """J_ii with its identity rows scaled to the stiffness beside them."""
+    s, P = S.subs[i], S.P
+    J, _ = S.local_jacobian(i, x, tr)
+    ue = np.concatenate([x, tr])[s["ldof"]]
+    m = (ue.sum(axis=1) ** 2 + (ue * ue).sum(axis=1)) / 12.0
+    d = np.zeros(len(x) + len(tr))
+    el = s["elems"]
+    for p in range(3):
+        np.add.at(d, s["ldof"][:, p], P.kappa[el] * (1.0 + P.beta * m) * P.G[el][:, p, p])
+    a = np.nonzero(s["dirV"])[0]
+    J[a] *= 2.0 ** (np.floor(np.log2(d[a])) + 1.0)[:, None]
+    return J
+
+
+def _interchanges(S, u):
+    """Columns that interchange, their 16-column panels from the first and from
+    the last, and the largest condition number, over the subdomains."""
+    cols, first, last, cond = 0, set(), set(), 0.0
+    for i, s in enumerate(S.subs):
+        J = _scaled(S, i, u[s["Vd"]], u[s["Gd"]])
+        _, piv, _, _ = band_lu_factor(J)
+        k = np.nonzero(piv != np.arange(len(piv)))[0]
+        cols += len(k)
+        first |= set(k // 16)
+        last |= set((len(piv) - 1) // 16 - k // 16)
+        cond = max(cond, np.linalg.cond(J))
+    return cols, first, last, cond
+
+
+def _solver(case, **kw):
+    from paper_2410_24138_amd import Solver
+    return Solver(case, coupling="one_level", **kw)
+
+
+# F_x from a rough iterate: the first Newton steps interchange.  Newton goes on
+# until its steps stagnate, at a smooth state (the load is 1), so that what is
+# left is the rounding of the last step: cond(J_ii) eps there, below 1e4 * 2e-16
+# with a band's few hundred operations per entry: 1e-10 of the largest entry.
+# A factorisation that lost an interchange solves another system and its
+# iteration does not converge.
+@pytest.mark.parametrize("precision,variant", [("fp64", 0), ("fp64", 1), ("fp64", 2), ("fp64", 3),
+                                               ("fp32_ir", 0), ("fp32_ir", 2), ("fp32_ir", 3)])
+@pytest.mark.parametrize("half,nyh,seed", SIZES)
+def test_local_newton(half, nyh, seed, precision, variant):
+    if (variant == 1 and half > 46) or (variant == 2 and half > 54):
+        pytest.skip("the band is too wide for these panels")
+    case, u, _ = _case(half, nyh, seed, False)
+    kw = dict(inner_rtol=1e-15, inner_eta=0.0, inner_maxit=60)
+    S = Schwarz(P1Problem(case), "one_level", **kw)
+    cols, first, last, _ = _interchanges(S, u)
+    assert cols >= 4 and 0 in first
+    ref = S.evaluate(u)
+    s = _solver(case, precision=precision, lu_variant=variant, **kw)
+    got = s.precond_residual(u).cpu().numpy()
+    assert np.abs(got - ref).max() <= 1e-10 * np.abs(ref).max()
+
+
+# The tangent at a rough state: the stopping rule is so wide that the iterate
+# itself is the local state.  W_i = J_ii^{-1} B_i loses cond(J_ii) eps; 16 times
+# that for the two factorisations and substitutions.
+@pytest.mark.parametrize("precision", ["fp64", "fp32_ir"])
+@pytest.mark.parametrize("sweep", [False, True])
+@pytest.mark.parametrize("half,nyh,seed", SIZES)
+def test_tangent(half, nyh, seed, sweep, precision):
+    from paper_2410_24138_amd import nls
+    if precision == "fp32_ir" and half > 54:
+        pytest.skip("one solve per product: with the binary32 factors of a Newton step")
+    case, u, rng = _case(half, nyh, seed, True)
+    v = rng.normal(size=len(u))
+    S = Schwarz(P1Problem(case), "one_level", inner_eta=1e30)
+    cols, first, last, cond = _interchanges(S, u)
+    assert cols >= 8 and 0 in first and 0 in last
+    S.evaluate(u)
+    ref = S.tangent(v)
+    s = _solver(case, precision=precision, inner_eta=1e30,
+                flags=nls.FLAG_TANGENT_SWEEP if sweep else 0)
+    assert not s.precond_residual(u).cpu().numpy().any()
+    got = s.tangent(v).cpu().numpy()
+    assert np.abs(got - ref).max() <= 16 * EPS * cond * np.abs(ref).max()
+
+
+# One Newton step with GMRES preconditioned by factors that interchange: the
+# solution of the linear system does not show a wrong factor, the number of
+# GMRES steps does.
+@pytest.mark.parametrize("half,nyh,seed", SIZES)
+def test_newton_krylov_schwarz_step(half, nyh, seed):
+    case, u, _ = _case(half, nyh, seed, True)
+    S = Schwarz(P1Problem(case), "one_level")
+    cols, first, last, _ = _interchanges(S, u)
+    assert cols >= 8 and 0 in first and 0 in last
+    kw = dict(gmres_rtol=1e-8, gmres_restart=200, gmres_maxit=200)
+    ref, st_ref = NKS(S).solve(u, maxit=1, **kw)
+    assert st_ref["gmres"][0] < 200
+    s = _solver(case, outer_maxit=1, **kw)
+    got, st, _ = s.solve_nks(u)
+    assert st["outer_its"] == 1 and abs(st["gmres_its"][0] - st_ref["gmres"][0]) <= 1
+    step = np.abs(ref - u).max()
+    # two solves to 1e-8 of the residual; cond of the preconditioned operator
+    # below 100 (it converges in tens of steps)
+    assert np.abs(got.cpu().numpy() - ref).max() <= 1e-6 * step
