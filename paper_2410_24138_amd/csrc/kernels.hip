@@ -1074,6 +1074,12 @@ __device__ __forceinline__ P* uniform(P* p) {
     return (P*)(((unsigned long long)hi << 32) | lo);
 }
 
+// Pivots below this are subnormal or zero; their reciprocal can be infinite.
+template <typename T>
+__device__ __forceinline__ T least_pivot() {
+    return sizeof(T) == 8 ? T(DBL_MIN) : T(FLT_MIN);
+}
+
 // The same value, unknown to the compiler: masks and offsets formed from it are
 // taken anew where they are used.  Those formed from the lane number itself do
 // not change in a loop, are hoisted out of it, and fill the registers (the
@@ -1312,8 +1318,9 @@ __device__ __forceinline__ int band_lu_gauss(int n_, int kl_, int ku_, const int
             if (!search) {
                 // no branch and no store between the steps.  The largest
                 // multiplier decides afterwards (the search takes entries
-                // within 2^-14 for equal); a zero pivot is left to the search
-                // as well.
+                // within 2^-14 for equal); a pivot without a finite reciprocal,
+                // whose multipliers are no numbers, is left to the search as
+                // well.
                 T lmax = T(0), pmin = fabs(rdlane(p[0], 0));
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
@@ -1336,7 +1343,7 @@ __device__ __forceinline__ int band_lu_gauss(int n_, int kl_, int ku_, const int
                     pmin = fmin(pmin, fabs(pv));
                     if (j == MID) lds_barrier();
                 }
-                redo = __ballot(lmax > T(1.0 + 0x1p-14)) != 0 || pmin == T(0);
+                redo = __ballot(lmax > T(1.0 + 0x1p-14)) != 0 || pmin < least_pivot<T>();
             }
             if (!redo) {
 #pragma unroll
@@ -1701,7 +1708,7 @@ __device__ __forceinline__ int band_lu_wide(int n_, int kl_, int ku_, const int*
                     pmin = fmin(pmin, fabs(pv));
                     if (j == MID) __syncthreads();
                 }
-                redo = __ballot(lmax > 1.0 + 0x1p-13) != 0 || pmin == 0.0;
+                redo = __ballot(lmax > 1.0 + 0x1p-13) != 0 || pmin < least_pivot<double>();
             }
             if (!redo) {
 #pragma unroll

@@ -144,3 +144,46 @@ def test_newton_krylov_schwarz_step(half, nyh, seed):
     # two solves to 1e-8 of the residual; cond of the preconditioned operator
     # below 100 (it converges in tens of steps)
     assert np.abs(got.cpu().numpy() - ref).max() <= 1e-6 * step
+
+
+# A pivot that is subnormal beside entries that are not: kappa = 2^-1000, beta =
+# -1, and u at the first unknown such that its diagonal entry cancels to 1e-10 of
+# its terms.  The tangent does not depend on kappa's size, so the oracle's is that
+# of kappa = 1.
+def test_subnormal_pivot():
+    case, u, rng = _case(13, 5, 0, False)
+    case["beta"] = -1.0
+    u *= 0.1
+    S = Schwarz(P1Problem(case), "one_level", inner_eta=1e30)
+    s0 = S.subs[0]
+    a = int(np.nonzero(~s0["dirV"])[0][0])
+    g = int(s0["Vd"][a])
+
+    def diagonal(x):
+        u[g] = x
+        return S.local_jacobian(0, u[s0["Vd"]], u[s0["Gd"]])[0][a, a]
+
+    xs = np.linspace(0.0, 4.0, 401)
+    d = np.array([diagonal(x) for x in xs])
+    k = int(np.nonzero(d[:-1] * d[1:] < 0.0)[0][0])
+    lo, hi = xs[k], xs[k + 1]
+    for _ in range(60):
+        mid = 0.5 * (lo + hi)
+        if np.sign(diagonal(mid)) == np.sign(d[k]):
+            lo = mid
+        else:
+            hi = mid
+        if abs(diagonal(mid)) <= 1e-10 * np.abs(d).max():
+            break
+    J = S.local_jacobian(0, u[s0["Vd"]], u[s0["Gd"]])[0]
+    assert 0.0 < abs(J[a, a]) <= 1e-9 * np.abs(J[a]).max()
+    assert abs(J[a, a]) * 2.0 ** -1000 < 2.0 ** -1022
+    cond = max(np.linalg.cond(_scaled(S, i, u[s["Vd"]], u[s["Gd"]])) for i, s in enumerate(S.subs))
+    v = rng.normal(size=len(u))
+    S.evaluate(u)
+    ref = S.tangent(v)
+    case["elem_coef"] = np.full(len(case["conn"]), 2.0 ** -1000)
+    s = _solver(case, inner_eta=1e30)
+    s.precond_residual(u)
+    got = s.tangent(v).cpu().numpy()
+    assert np.abs(got - ref).max() <= 16 * EPS * cond * np.abs(ref).max()
