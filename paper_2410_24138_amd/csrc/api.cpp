@@ -1535,7 +1535,7 @@ static int gmres(nls_handle* h, const double* b, double* x, int* its_out, bool g
     const hipStream_t gs = graph ? h->gstream : h->stream;
     const double tol = h->opt.gmres_rtol * bn;
     HIPCHK(hipMemcpyAsync(h->gtol, &tol, sizeof(double), hipMemcpyHostToDevice, h->stream));
-    std::vector<double> H((size_t)(m + 1) * m), g(m + 1), y(m), g0(m + 1);
+    std::vector<double> H, g, y;  // of the steps a cycle took
     int its = 0;
     bool first = true;
     while (its < h->opt.gmres_maxit) {
@@ -1554,10 +1554,8 @@ static int gmres(nls_handle* h, const double* b, double* x, int* its_out, bool g
         if (beta <= tol) break;
         HIPCHK(hipMemcpyAsync(h->hn2, &beta2, sizeof(double), hipMemcpyHostToDevice, h->stream));
         HIPCHK(launch_scale_by(h->V, h->hn2, h->V, N, h->stream));
-        std::fill(g0.begin(), g0.end(), 0.0);
-        g0[0] = beta;
         const int st0[2] = {0, 0};
-        HIPCHK(hipMemcpyAsync(h->gd, g0.data(), (m + 1) * sizeof(double), hipMemcpyHostToDevice, h->stream));
+        HIPCHK(hipMemcpyAsync(h->gd, &beta, sizeof(double), hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->gst, st0, sizeof(st0), hipMemcpyHostToDevice, h->stream));
         int j = 0, conv = 0;
         if (!graph) {
@@ -1590,8 +1588,11 @@ static int gmres(nls_handle* h, const double* b, double* x, int* its_out, bool g
             }
         }
         if (j == 0) break;
+        H.resize((size_t)j * m);  // the first j rows
+        g.resize(j);
+        y.resize(j);
         HIPCHK(hipMemcpyAsync(H.data(), h->Hd, H.size() * sizeof(double), hipMemcpyDeviceToHost, gs));
-        HIPCHK(hipMemcpyAsync(g.data(), h->gd, (m + 1) * sizeof(double), hipMemcpyDeviceToHost, gs));
+        HIPCHK(hipMemcpyAsync(g.data(), h->gd, j * sizeof(double), hipMemcpyDeviceToHost, gs));
         HIPCHK(hipStreamSynchronize(gs));
         for (int i = j - 1; i >= 0; --i) {
             double s = g[i];

@@ -4641,7 +4641,7 @@ __device__ void gmres_givens_step(const GmresDev& G, int j) {
     double a = G.h1[0] + G.h2[0];
     for (int i = 0; i < j; ++i) {
         const double b = G.h1[i + 1] + G.h2[i + 1];
-        H[i * m + j] = G.cs[i] * a + G.sn[i] * b;
+        H[(int64_t)i * m + j] = G.cs[i] * a + G.sn[i] * b;
         a = -G.sn[i] * a + G.cs[i] * b;
     }
     const double b = sqrt(G.hn2[0]);
@@ -4649,8 +4649,8 @@ __device__ void gmres_givens_step(const GmresDev& G, int j) {
     const double c = den > 0.0 ? a / den : 1.0, sn = den > 0.0 ? b / den : 0.0;
     G.cs[j] = c;
     G.sn[j] = sn;
-    H[j * m + j] = den;
-    H[(j + 1) * m + j] = 0.0;
+    H[(int64_t)j * m + j] = den;
+    H[(int64_t)(j + 1) * m + j] = 0.0;
     const double gj = G.g[j];
     G.g[j + 1] = -sn * gj;
     G.g[j] = c * gj;
@@ -5006,6 +5006,20 @@ hipError_t launch_arnoldi_gs(const double* V, int64_t ld, int m, double* w, int 
                              double* vnext, int nb, hipStream_t s, double* partial2) {
     const int lds = m * (int)sizeof(double);
     k_mdot_partial<<<nb, NLS_BLOCK, 0, s>>>(V, ld, m, w, n, partial);
+    if (m > 2048) {
+        // long cycles: a column's totals would need up to all of the LDS (more
+        // than a launch may have from 8,192 steps on) and every block would add
+        // all of them up again; they go through global memory.  Cycles of 2,300
+        // and 4,000 steps, 9,021 dofs: 4.44 and 13.5 s (4.48 and 13.8 s)
+        k_mdot_final<<<m, 256, 0, s>>>(partial, nb, m, h1);
+        k_maxpy<<<nblocks(n), NLS_BLOCK, 0, s>>>(V, ld, m, h1, w, n, 1.0);
+        k_mdot_partial<<<nb, NLS_BLOCK, 0, s>>>(V, ld, m, w, n, partial2);
+        k_mdot_final<<<m, 256, 0, s>>>(partial2, nb, m, h2);
+        k_maxpy<<<nblocks(n), NLS_BLOCK, 0, s>>>(V, ld, m, h2, w, n, 1.0);
+        k_mdot_partial<<<nb, NLS_BLOCK, 0, s>>>(w, n, 1, w, n, pnorm);
+        k_scale_givens_totals<<<nblocks(n), NLS_BLOCK, 0, s>>>(w, vnext, n, pnorm, nb, G, j);
+        return hipGetLastError();
+    }
     k_maxpy_mdot_totals<<<nb, NLS_BLOCK, lds, s>>>(V, ld, m, partial, nb, h1, w, n, partial2);
     k_maxpy_norm_totals<<<nb, NLS_BLOCK, lds, s>>>(V, ld, m, partial2, nb, h2, w, n, pnorm);
     k_scale_givens_totals<<<nblocks(n), NLS_BLOCK, 0, s>>>(w, vnext, n, pnorm, nb, G, j);
