@@ -1708,7 +1708,7 @@ __device__ __forceinline__ int band_lu_wide(int n_, int kl_, int ku_, const int*
                     pmin = fmin(pmin, fabs(pv));
                     if (j == MID) __syncthreads();
                 }
-                redo = __ballot(lmax > 1.0 + 0x1p-13) != 0 || pmin < least_pivot<double>();
+                redo = __ballot(lmax > 1.0 + 0x1p-14) != 0 || pmin < least_pivot<double>();
             }
             if (!redo) {
 #pragma unroll
@@ -1737,15 +1737,18 @@ __device__ __forceinline__ int band_lu_wide(int n_, int kl_, int ku_, const int*
                     int hp = b0 == 0, pl = __ffsll(b0 ? b0 : b1) - 1, d = j;
                     const double aj = fabs(rdlane(hp ? p[1][j] : p[0][j], pl));
                     if (__ballot((cand[0] && av[0] > aj) || (cand[1] && av[1] > aj)) != 0) {
-                        unsigned key = 0u;
+                        // wave_argmax_hi's rule (entries within 2^-14 are equal,
+                        // the lowest position wins); two rows per lane leave the
+                        // positions no room in its key, so they are compared next
+                        unsigned key[2];
 #pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            const double a = av[h] <= DBL_MAX ? av[h] : DBL_MAX;
-                            const unsigned kh =
-                                ((unsigned)__double2hiint(a) & ~127u) | (unsigned)(127 - pos[h]);
-                            key = max(key, cand[h] ? kh : 0u);
-                        }
-                        d = 127 - (int)(wave_umax(key) & 127u);
+                        for (int h = 0; h < 2; ++h)
+                            key[h] = cand[h] ? (unsigned)__double2hiint(av[h] <= DBL_MAX ? av[h] : DBL_MAX) & ~63u : 0u;
+                        const unsigned top = wave_umax(max(key[0], key[1]));
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+                            key[h] = cand[h] && key[h] == top ? (unsigned)(128 - pos[h]) : 0u;
+                        d = 128 - (int)wave_umax(max(key[0], key[1]));
                         const unsigned long long c0 = __ballot(cand[0] && pos[0] == d),
                                                  c1 = __ballot(cand[1] && pos[1] == d);
                         hp = c0 == 0;
