@@ -391,7 +391,9 @@ __global__ void __launch_bounds__(256) k_grad_partial(GradArgs g) {
     float* out = g.part + (size_t)blockIdx.y * g.nparam;
     const int nt = in / GBN, ntile = nt * (NLS_G_WIDTH / GBM);
     if (q >= ntile) {
-        // column sums: 16 rows at a time, 16 columns per four threads' rows
+        // column sums: a column per lane, every fourth row per wavefront, the
+        // loads of eight rows at a time in flight; then the four partial sums
+        // in a fixed order
         __shared__ float red[256];
         const int c = 64 * (q - ntile) + (threadIdx.x & 63), part = threadIdx.x >> 6;
         float s = 0.f;

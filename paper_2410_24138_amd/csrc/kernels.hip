@@ -352,10 +352,11 @@ __device__ __forceinline__ void local_residual(const DevMesh& M, const DevMaps& 
 // high valence) add into jval in place.
 // ----------------------------------------------------------------------------
 //
-// SCALED (the local linear systems): an identity row is multiplied by the
-// power of two above the diagonal entry it would have without its Dirichlet
-// condition, and rb (may be null), the system's right-hand side, with it.  The
-// factorisation then keeps its pivot like its neighbours keep theirs (a 1
+// SCALED (the local linear systems): an identity row is multiplied by a power
+// of two, and rb (may be null), the system's right-hand side, with it: the next
+// one above the diagonal entry that the row's elements would give it (for
+// diffusion without the term from the coefficient's derivative).  The
+// factorisation then keeps its pivot as its neighbours mostly keep theirs (a 1
 // beside their entries costs an interchange for every Dirichlet dof of the
 // patch); the scaling is exact and the solution the same.
 template <bool ELAST, bool SCALED = false>
