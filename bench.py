@@ -57,8 +57,8 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per dispatch measured with rocprofv3 FETCH_SIZE/WRITE_SIZE (two
 # passes, calibrated against a 256 MiB copy; profiles/hbm_traffic_*.md), valid
 # only for the kernel source they were taken with.
-MEASURED_TRAFFIC = {"kernels_sha1": "1b8d4f8c1ba10a1092991d3e2d9452176e14f1b7",
-                    "bytes": {"k_local_newton": 1729753495, "k_local_factor": 397416786, "k_tangent_blocks": 359828439, "k_tangent_mfma": 3106679445, "k_tangent_gemv": 280765810, "k_coarse_galerkin": 84064600, "k_coarse_galerkin_sum": 97875451, "k_coarse_lu": 1517538, "k_coarse_inv_blocks": 1150762, "k_coarse_inv_mfma": 20875817, "k_coarse_apply_inverse": 4101910, "k_mdot_partial": 23556716, "k_maxpy_mdot_totals": 31341962, "k_prolong": 27326741, "k_coarse_ty": 20663292, "k_coarse_q": 80454912}}
+MEASURED_TRAFFIC = {"kernels_sha1": "026a8b9e82e562415cefc00c8cefc972226bcf7d",
+                    "bytes": {"k_local_newton": 949156317, "k_local_factor": 401425492, "k_tangent_blocks": 359825431, "k_tangent_mfma": 3105599820, "k_tangent_gemv": 280772161, "k_coarse_galerkin": 84084374, "k_coarse_galerkin_sum": 98666502, "k_coarse_q": 80615036, "k_coarse_lu": 1591898, "k_coarse_inv_blocks": 1150762, "k_coarse_inv_mfma": 20875305, "k_coarse_apply_inverse": 4132755, "k_mdot_partial": 23556652, "k_maxpy_mdot_totals": 31324972, "k_prolong": 27314582, "k_coarse_ty": 20665116}}
 
 
 def unit_work(case, elem_bytes=8):
