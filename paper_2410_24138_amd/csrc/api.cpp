@@ -14,6 +14,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <climits>
 #include <memory>
 #include <numeric>
 #include <thread>
@@ -1477,27 +1478,37 @@ static int block_graph(nls_handle* h, int b, hipGraphExec_t* out) {
 // `budget` of them, until one meets the tolerance: *used counts them (up to
 // the one that met it), *conv tells whether one did.  The host reads a step's
 // state while the next step is already enqueued, so the device does not wait
-// for it; a step that turns out not to be needed leaves the state alone.
+// for it; a step that turns out not to be needed leaves the state alone.  The
+// words that a step's copy fills are marked before it is enqueued: a mark that is
+// still there when the step's event has passed means a wait for the whole
+// stream, and only a count that the steps so far allow is taken.
 // Where a step solves band systems (no explicit tangent blocks) it costs more
 // than that wait, and nothing is enqueued ahead.
 static int gmres_steps(nls_handle* h, int budget, int* used, int* conv) {
     const int ahead = (h->tangent_w && !h->nks_mode) ? 2 : 1;
     for (hipEvent_t& e : h->sev)
         if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    const int last = std::min(h->m, budget);
+    const int last = std::min(h->m, budget), unread = INT_MIN;
     int issued = 0, done = 0;
     *conv = 0;
+    volatile int* const state = pin_graph(h);
     while (done < last) {
         while (issued < last && issued - done < ahead) {
             RC(arnoldi_step(h, issued, h->stream));
+            state[2 * (issued & 1)] = unread;
             HIPCHK(hipMemcpyAsync(pin_graph(h) + 2 * (issued & 1), h->gst, 2 * sizeof(int),
                                   hipMemcpyDeviceToHost, h->stream));
             HIPCHK(hipEventRecord(h->sev[issued & 1], h->stream));
             ++issued;
         }
         HIPCHK(hipEventSynchronize(h->sev[done & 1]));
-        const int st = pin_graph(h)[2 * (done & 1)];
+        if (state[2 * (done & 1)] == unread) RC(sync(h));
+        const int st = state[2 * (done & 1)];
         ++done;
+        if (st == unread || st > issued) {
+            RC(sync(h));
+            return fail(h, NLS_EHIP, "a GMRES step's state was not read");
+        }
         if (st < 0) {
             RC(sync(h));
             return fail(h, NLS_ENAN, "GMRES breakdown (non-finite)");
