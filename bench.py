@@ -57,8 +57,8 @@ HBM_PEAK_GBS = 8000.0
 # HBM bytes per dispatch measured with rocprofv3 FETCH_SIZE/WRITE_SIZE (two
 # passes, calibrated against a 256 MiB copy; profiles/hbm_traffic_*.md), valid
 # only for the kernel source they were taken with.
-MEASURED_TRAFFIC = {"kernels_sha1": "026a8b9e82e562415cefc00c8cefc972226bcf7d",
-                    "bytes": {"k_local_newton": 949156317, "k_local_factor": 401425492, "k_tangent_blocks": 359825431, "k_tangent_mfma": 3105599820, "k_tangent_gemv": 280772161, "k_coarse_galerkin": 84084374, "k_coarse_galerkin_sum": 98666502, "k_coarse_q": 80615036, "k_coarse_lu": 1591898, "k_coarse_inv_blocks": 1150762, "k_coarse_inv_mfma": 20875305, "k_coarse_apply_inverse": 4132755, "k_mdot_partial": 23556652, "k_maxpy_mdot_totals": 31324972, "k_prolong": 27314582, "k_coarse_ty": 20665116}}
+MEASURED_TRAFFIC = {"kernels_sha1": "7d799df23dd632f0474f4b2c77c0c87a7117141e",
+                    "bytes": {"k_local_newton": 949356520, "k_local_factor": 401437267, "k_tangent_blocks": 359828756, "k_tangent_mfma": 3114583045, "k_tangent_gemv": 280772959, "k_coarse_galerkin": 84059686, "k_coarse_galerkin_sum": 97947276, "k_coarse_q": 80650522, "k_coarse_lu": 1579737, "k_coarse_inv_blocks": 1150759, "k_coarse_inv_mfma": 20868098, "k_coarse_apply_inverse": 4132741, "k_mdot_partial": 23556509, "k_maxpy_mdot_totals": 31300334, "k_prolong": 27314498, "k_coarse_ty": 20665207}}
 
 
 def unit_work(case, elem_bytes=8):
